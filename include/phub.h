@@ -132,7 +132,9 @@ typedef struct phub_options {
                                bursts take none of it (they stream as fast as
                                they cache): momentum SGD and plain SGD with
                                6 to 16, 20, 24 or 32 workers, Adam with 14 to
-                               16, 20, 24 or 32, not unfused.  A job that
+                               16, 20, 24 or 32, and any other count above 16
+                               whose gradients and state together exceed the
+                               budget's 256 MiB; not unfused.  A job that
                                will step with pushpull (whose kernels write
                                the model buffers and have no burst
                                write-back) gains from an explicit budget:

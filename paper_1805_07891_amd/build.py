@@ -9,9 +9,11 @@ the step defines; packed fp32 instructions are disabled.
 
 from __future__ import annotations
 
+import concurrent.futures
 import os
 import subprocess
 import sys
+import tempfile
 from typing import Sequence
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -25,8 +27,10 @@ PROBE_LIB = os.path.join(PKG, "libphub_probe.so")
 GRADIENTS_CACHED_LIB = os.path.join(PKG, "libphub_gradients_cached.so")
 PROBE_SOURCES = ["probe.hip"]
 
-SOURCES = ["plan.cpp", "phub_api.cpp", "fused_step.hip", "step_noalloc.hip"]
-HEADERS = ["plan.hpp", "kernels.hpp"]
+SOURCES = ["plan.cpp", "phub_api.cpp", "fused_step.hip", "fused_many.hip", "step_noalloc.hip"]
+HEADERS = ["plan.hpp", "kernels.hpp", "device.hpp"]
+# fused_step.hip holds hundreds of kernels: it is compiled in this many parts
+STEP_PARTS = 8
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
@@ -46,16 +50,29 @@ FLAGS = [
 
 def build(out: str = LIB, defines: Sequence[str] = (), extra: Sequence[str] = (),
           verbose: bool = False) -> str:
-    """Compile and link the library; returns its path.  ``defines`` are
-    extra -D settings (used for launch-shape sweeps)."""
-    srcs = [os.path.join(CSRC, s) for s in SOURCES]
-    tmp = out + ".tmp"
-    cmd = [HIPCC, *FLAGS, f"-I{INCLUDE}", f"-I{CSRC}", *[f"-D{d}" for d in defines], *extra,
-           *srcs, "-o", tmp]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    subprocess.check_call(cmd)
-    os.replace(tmp, out)
+    """Compile the sources side by side and link the library; returns its
+    path.  ``defines`` are extra -D settings (used for launch-shape sweeps)."""
+    flags = [f for f in FLAGS if f != "-shared"]
+    units = []  # (source, its own defines), the longest compilations first
+    for s in sorted(SOURCES, key=lambda s: s != "fused_step.hip"):
+        parts = range(STEP_PARTS) if s == "fused_step.hip" else (None,)
+        units += [(s, [] if p is None else [f"PHUB_STEP_PART={p}"]) for p in parts]
+    with tempfile.TemporaryDirectory(dir=os.path.dirname(os.path.abspath(out))) as tmp:
+        def compile_one(i: int) -> str:
+            src, own = units[i]
+            obj = os.path.join(tmp, f"{i}.o")
+            cmd = [HIPCC, *flags, f"-I{INCLUDE}", f"-I{CSRC}", *[f"-D{d}" for d in defines],
+                   *[f"-D{d}" for d in own], *extra, "-c", os.path.join(CSRC, src), "-o", obj]
+            if verbose:
+                print(" ".join(cmd), flush=True)
+            subprocess.check_call(cmd)
+            return obj
+
+        with concurrent.futures.ThreadPoolExecutor(min(8, os.cpu_count() or 1)) as pool:
+            objs = list(pool.map(compile_one, range(len(units))))
+        lib = os.path.join(tmp, "lib.so")
+        subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", lib])
+        os.replace(lib, out)
     return out
 
 

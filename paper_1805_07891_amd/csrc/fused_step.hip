@@ -52,196 +52,12 @@
 #include <type_traits>
 #include <utility>
 
+#include "device.hpp"
 #include "kernels.hpp"
 
 namespace phub {
 
-typedef float f4 __attribute__((ext_vector_type(4)));
-
 namespace {
-
-constexpr int kWavesPerBlock = kBlockThreads / 64;
-
-// ------------------------------------------------------------- optimizers
-
-// State arrays of each optimizer, W first.
-template <int OPT>
-constexpr int kStates = OPT == kOptSgd ? 1 : (OPT == kOptAdam ? 3 : 2);
-
-// Correctly rounded single-precision square root.  The hardware square
-// root (with the compiler's denormal scaling) is within one ulp, so the
-// correctly rounded root is y, or its neighbour below or above.  The
-// midpoints between neighbours have at most 25 significant bits, so their
-// squares are exact in double; comparing x with them decides exactly
-// (a float's square root is never a midpoint, so there are no ties).
-__device__ __forceinline__ float sqrt_rn(float x) {
-    const float y = __builtin_sqrtf(x);
-    if (!(x > 0.0f) || !(y < __builtin_huge_valf())) return y;  // 0, < 0, NaN, inf
-    const uint32_t yb = __builtin_bit_cast(uint32_t, y);
-    const float down = __builtin_bit_cast(float, yb - 1u);
-    const float up = __builtin_bit_cast(float, yb + 1u);
-    const double lo = 0.5 * (double(down) + double(y));
-    const double hi = 0.5 * (double(y) + double(up));
-    const double xd = double(x);
-    if (xd < lo * lo) return down;
-    if (xd > hi * hi) return up;
-    return y;
-}
-
-// One element: st[0] = w, st[1] = m, st[2] = v, updated in place.
-template <int OPT>
-__device__ __forceinline__ void update(float s, float* st, OptArgs o) {
-    if constexpr (OPT == kOptSgd) {
-        const float d = __builtin_fmaf(o.wd, st[0], s);
-        st[0] = __builtin_fmaf(o.nlr, d, st[0]);
-    } else if constexpr (OPT == kOptAdam) {
-        const float d = __builtin_fmaf(o.wd, st[0], s);
-        const float m = __builtin_fmaf(o.b1, st[1], o.c1 * d);
-        const float dd = d * d;
-        const float v = __builtin_fmaf(o.b2, st[2], o.c2 * dd);
-        const float den = sqrt_rn(v * o.k2) + o.eps;
-        const float q = __fdiv_rn(o.k1 * m, den);
-        st[0] = st[0] - q;
-        st[1] = m;
-        st[2] = v;
-    } else {
-        constexpr bool NEST = OPT == kOptNesterov;
-        const float d = __builtin_fmaf(o.wd, st[0], s);
-        const float m1 = __builtin_fmaf(o.mu, st[1], d);
-        const float u = NEST ? __builtin_fmaf(o.mu, m1, d) : m1;
-        st[0] = __builtin_fmaf(o.nlr, u, st[0]);
-        st[1] = m1;
-    }
-}
-
-// Four elements at once (a float4 of each array).
-template <int OPT>
-__device__ __forceinline__ void update4(const f4& s, f4* st, OptArgs o) {
-    if constexpr (OPT == kOptAdam) {
-        // the square root and division per component, correctly rounded
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            float e[3] = {st[0][c], st[1][c], st[2][c]};
-            update<OPT>(s[c], e, o);
-            st[0][c] = e[0];
-            st[1][c] = e[1];
-            st[2][c] = e[2];
-        }
-    } else if constexpr (OPT == kOptSgd) {
-        const f4 vwd = o.wd, vnlr = o.nlr;
-        const f4 d = __builtin_elementwise_fma(vwd, st[0], s);
-        st[0] = __builtin_elementwise_fma(vnlr, d, st[0]);
-    } else {
-        constexpr bool NEST = OPT == kOptNesterov;
-        const f4 vwd = o.wd, vmu = o.mu, vnlr = o.nlr;
-        const f4 d = __builtin_elementwise_fma(vwd, st[0], s);
-        const f4 m1 = __builtin_elementwise_fma(vmu, st[1], d);
-        const f4 u = NEST ? __builtin_elementwise_fma(vmu, m1, d) : m1;
-        st[0] = __builtin_elementwise_fma(vnlr, u, st[0]);
-        st[1] = m1;
-    }
-}
-
-// --------------------------------------------------------- memory access
-
-// Gradient pointers come from a table in memory, so the compiler cannot tell
-// they address global memory and would emit flat loads (which wait on both
-// the vector and the LDS counters).  Casting to the global address space
-// gives global_load_dwordx4 with the uniform base in SGPRs and a 32-bit
-// per-lane offset.
-#define PHUB_GLOBAL __attribute__((address_space(1)))
-#define PHUB_LDS __attribute__((address_space(3)))
-
-// Gradient loads (and the unfused variant's sum buffer): non-temporal, as
-// each gradient byte is read once.  A build with PHUB_GRADIENT_LOADS_CACHED
-// set loads them cache-allocating instead: the ablation of caching the
-// gradients beside the model (the paper's Table 4).
-#ifndef PHUB_GRADIENT_LOADS_CACHED
-#define PHUB_GRADIENT_LOADS_CACHED 0
-#endif
-__device__ __forceinline__ f4 load_stream(const float* base, uint32_t byte_off) {
-    const PHUB_GLOBAL char* b = (const PHUB_GLOBAL char*)base;
-#if PHUB_GRADIENT_LOADS_CACHED
-    return *(const PHUB_GLOBAL f4*)(b + byte_off);
-#else
-    return __builtin_nontemporal_load((const PHUB_GLOBAL f4*)(b + byte_off));
-#endif
-}
-
-// State accesses.  The policy is a template argument resolved with
-// `if constexpr`: written as a run-time choice between two loads of the same
-// address, the compiler merges the two loads into one and drops the
-// non-temporal hint.
-template <bool RES>
-__device__ __forceinline__ f4 load_wm(const float* base, uint32_t byte_off) {
-    const PHUB_GLOBAL f4* a = (const PHUB_GLOBAL f4*)((const PHUB_GLOBAL char*)base + byte_off);
-    if constexpr (RES)
-        return *a;
-    else
-        return __builtin_nontemporal_load(a);
-}
-
-template <bool RES>
-__device__ __forceinline__ void store_wm(float* base, uint32_t byte_off, const f4& v) {
-    PHUB_GLOBAL f4* a = (PHUB_GLOBAL f4*)((PHUB_GLOBAL char*)base + byte_off);
-    if constexpr (RES)
-        *a = v;
-    else
-        __builtin_nontemporal_store(v, a);
-}
-
-// A float4 of stashed state written back in a write phase: a buffer store
-// (the compiler tracks it like any other store; the base in SGPRs, a 32-bit
-// lane offset) with the cache policy bits of gfx950 given directly:
-// non-temporal (2) with the sc1 bit (16).  Measured in the write phases
-// against the non-temporal global store: +0.1 to +0.9 points on 8- and
-// 16-worker jobs and +0.5 on four tenants; plain (cache-allocating) stores
-// were 13-15 points below.  The descriptor covers 2 GB from the base, far
-// beyond a tile's offsets (below 17 MB).
-constexpr int kBufferWord3 = 0x00020000;  // buffer descriptor's format word on gfx9
-constexpr int kWriteBackCachePolicy = 2 | 16;
-__device__ __forceinline__ void store_wb(float* base, uint32_t byte_off, const f4& v) {
-    const __amdgpu_buffer_rsrc_t r =
-        __builtin_amdgcn_make_buffer_rsrc(base, 0, 0x7fffffff, kBufferWord3);
-    __builtin_amdgcn_raw_buffer_store_b128(v, r, int(byte_off), 0, kWriteBackCachePolicy);
-}
-
-// Updated weights written to a worker's model buffer (pushpull): written
-// once and not read by the step, so non-temporal.
-__device__ __forceinline__ void store_out(float* base, uint32_t byte_off, const f4& v) {
-    __builtin_nontemporal_store(v, (PHUB_GLOBAL f4*)((PHUB_GLOBAL char*)base + byte_off));
-}
-
-__device__ __forceinline__ float load1(const float* base, int64_t i) {
-    return ((const PHUB_GLOBAL float*)base)[i];
-}
-
-__device__ __forceinline__ void store1(float* base, int64_t i, float v) {
-    ((PHUB_GLOBAL float*)base)[i] = v;
-}
-
-__device__ __forceinline__ uint32_t wave_index() {
-    return __builtin_amdgcn_readfirstlane(blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6));
-}
-
-// The kernel arguments are __restrict__: the schedule and the pointer table
-// are never written by the kernel and the state never aliases the
-// gradients, which lets the compiler fetch descriptors and pointers with
-// scalar loads.
-#define PHUB_KERNEL_ARGS                                                                  \
-    const DevTile* __restrict__ tiles, const int32_t* __restrict__ tile_begin,            \
-        const DevRem* __restrict__ rems, const int32_t* __restrict__ rem_begin,           \
-        const WaveHead* __restrict__ heads,                                               \
-        const float* const* __restrict__ grads, float* const* __restrict__ outs,          \
-        float* __restrict__ weights, float* __restrict__ moments,                         \
-        float* __restrict__ second, OptArgs o, int num_workers,                           \
-        const DevTile* __restrict__ pool, int32_t pool_count,                             \
-        unsigned long long* __restrict__ pool_counters, uint64_t pool_launch
-
-// Splits a tile's float4 index into a part folded into the base pointers
-// (a multiple of 2^20 float4, 16 MB) and a low part that keeps the per-lane
-// 32-bit byte offset far from overflow.
-constexpr uint32_t kVecLowMask = (1u << 20) - 1;
 
 // ------------------------------------------------------------ full tiles
 
@@ -435,16 +251,6 @@ struct TilePipe {
     f4 acc[kVecPerLane];      // running gradient sums
     f4 sv[S][kVecPerLane];    // the state of each piece
 };
-
-// Whether the device's wall clock is inside a write window of the burst
-// write-back (the same answer for every lane: the clock is a scalar).  The
-// low 32 bits of the clock wrap every 43 s at 100 MHz; the wrap shifts the
-// phase of the periods once, which costs nothing but a slightly misplaced
-// window.
-__device__ __forceinline__ bool in_write_window(uint32_t period, uint32_t window) {
-    const uint32_t now = uint32_t(wall_clock64());
-    return now % period < window;
-}
 
 // Writes back the stashed state of the wave's tiles [t0, t1] (streamed
 // bin), tile by tile, each tile's S arrays piece by piece; tile t's state
@@ -947,8 +753,9 @@ __global__ __launch_bounds__(kBlockThreads) PHUB_ONE_WAVE_PER_SIMD void fused_st
                                     h.first_rem_streamed, grads, outs, state, o);
 }
 
-// Any N: workers taken in batches of kBatch, each batch's loads in flight
-// together, the running sum carried across batches in worker order.
+// Pushpull with any N (fused_many.hip has the other steps): workers taken in
+// batches of kBatch, each batch's loads in flight together, the running sum
+// carried across batches in worker order.
 constexpr int kBatch = 8;
 
 __device__ __forceinline__ f4 sum_any(const float* const* kp, int n, int64_t offset,
@@ -990,7 +797,7 @@ __device__ __forceinline__ void sum_any_pieces(const float* const* kp, int n, in
     }
 }
 
-template <int OPT, bool RES, bool PULL>
+template <int OPT, bool RES>
 __device__ __forceinline__ void run_any(const float* const* kp, float* const* ko, int n,
                                         int64_t offset, float* const* stb, uint32_t nvec,
                                         uint32_t rem, OptArgs o) {
@@ -1012,8 +819,7 @@ __device__ __forceinline__ void run_any(const float* const* kp, float* const* ko
             update4<OPT>(sum[u], st[u], o);
 #pragma unroll
             for (int i = 0; i < S; ++i) store_wm<RES>(stb[i], bo + u * 1024u, st[u][i]);
-            if constexpr (PULL)
-                for (int w = 0; w < n; ++w) store_out(ko[w] + offset, bo + u * 1024u, st[u][0]);
+            for (int w = 0; w < n; ++w) store_out(ko[w] + offset, bo + u * 1024u, st[u][0]);
         }
     }
     for (uint32_t v = nfull + lane; v < nvec; v += 64u) {
@@ -1025,8 +831,7 @@ __device__ __forceinline__ void run_any(const float* const* kp, float* const* ko
         update4<OPT>(s, st, o);
 #pragma unroll
         for (int i = 0; i < S; ++i) store_wm<RES>(stb[i], bo, st[i]);
-        if constexpr (PULL)
-            for (int w = 0; w < n; ++w) store_out(ko[w] + offset, bo, st[0]);
+        for (int w = 0; w < n; ++w) store_out(ko[w] + offset, bo, st[0]);
     }
     if (lane < rem) {
         const int64_t i = int64_t(nvec) * 4 + lane;
@@ -1038,13 +843,12 @@ __device__ __forceinline__ void run_any(const float* const* kp, float* const* ko
         update<OPT>(s, st, o);
 #pragma unroll
         for (int k = 0; k < S; ++k) store1(stb[k], i, st[k]);
-        if constexpr (PULL)
-            for (int w = 0; w < n; ++w) store1(ko[w] + offset, i, st[0]);
+        for (int w = 0; w < n; ++w) store1(ko[w] + offset, i, st[0]);
     }
 }
 
 // One bin of the any-N kernel: full tiles [tb, te), then remainders [rb, re).
-template <int OPT, bool RES, bool PULL>
+template <int OPT, bool RES>
 __device__ __forceinline__ void any_bin(const DevTile* __restrict__ tiles, int32_t tb, int32_t te,
                                         const DevRem* __restrict__ rems, int32_t rb, int32_t re,
                                         const float* const* __restrict__ grads,
@@ -1056,31 +860,29 @@ __device__ __forceinline__ void any_bin(const DevTile* __restrict__ tiles, int32
         float* stb[S];
 #pragma unroll
         for (int i = 0; i < S; ++i) stb[i] = state[i] + tl.arena_offset;
-        run_any<OPT, RES, PULL>(grads + int64_t(tl.key) * n,
-                                PULL ? outs + int64_t(tl.key) * n : nullptr, n,
-                                int64_t(tl.vec) * 4, stb, uint32_t(kTileElems / 4), 0u, o);
+        run_any<OPT, RES>(grads + int64_t(tl.key) * n, outs + int64_t(tl.key) * n, n,
+                          int64_t(tl.vec) * 4, stb, uint32_t(kTileElems / 4), 0u, o);
     }
     for (int32_t r = rb; r < re; ++r) {
         const DevRem rm = rems[r];
         float* stb[S];
 #pragma unroll
         for (int i = 0; i < S; ++i) stb[i] = state[i] + rm.arena_offset;
-        run_any<OPT, RES, PULL>(grads + int64_t(rm.key) * n,
-                                PULL ? outs + int64_t(rm.key) * n : nullptr, n, rm.offset, stb,
-                                uint32_t(rm.count) >> 2, uint32_t(rm.count) & 3u, o);
+        run_any<OPT, RES>(grads + int64_t(rm.key) * n, outs + int64_t(rm.key) * n, n, rm.offset,
+                          stb, uint32_t(rm.count) >> 2, uint32_t(rm.count) & 3u, o);
     }
 }
 
-template <int OPT, bool PULL>
+template <int OPT>
 __global__ __launch_bounds__(kBlockThreads) void fused_step_any(PHUB_KERNEL_ARGS) {
     float* const state[3] = {weights, moments, second};
     const uint32_t wave = wave_index();
     const uint32_t bins = gridDim.x * kWavesPerBlock;
-    any_bin<OPT, false, PULL>(tiles, tile_begin[bins + wave], tile_begin[bins + wave + 1], rems,
-                              rem_begin[bins + wave], rem_begin[bins + wave + 1], grads, outs,
-                              state, num_workers, o);
-    any_bin<OPT, true, PULL>(tiles, tile_begin[wave], tile_begin[wave + 1], rems, rem_begin[wave],
-                             rem_begin[wave + 1], grads, outs, state, num_workers, o);
+    any_bin<OPT, false>(tiles, tile_begin[bins + wave], tile_begin[bins + wave + 1], rems,
+                        rem_begin[bins + wave], rem_begin[bins + wave + 1], grads, outs, state,
+                        num_workers, o);
+    any_bin<OPT, true>(tiles, tile_begin[wave], tile_begin[wave + 1], rems, rem_begin[wave],
+                       rem_begin[wave + 1], grads, outs, state, num_workers, o);
 }
 
 // Ablation: the unfused ("wide") form of the step, kept to measure what
@@ -1189,9 +991,13 @@ __global__ __launch_bounds__(kBlockThreads) void optimize_only(PHUB_KERNEL_ARGS,
 
 template <int OPT, bool PULL>
 hipError_t launch_any(const StepParams& p, int grid, hipStream_t stream) {
-    hipLaunchKernelGGL((fused_step_any<OPT, PULL>), dim3(grid), dim3(kBlockThreads), 0, stream,
-                       PHUB_LAUNCH_ARGS);
-    return hipGetLastError();
+    if constexpr (PULL) {
+        hipLaunchKernelGGL((fused_step_any<OPT>), dim3(grid), dim3(kBlockThreads), 0, stream,
+                           PHUB_LAUNCH_ARGS);
+        return hipGetLastError();
+    } else {
+        return launch_fused_step_many(p, OPT, grid, stream);
+    }
 }
 
 template <int NW, int OPT, bool PULL>
@@ -1245,15 +1051,48 @@ hipError_t launch_unfused(const StepParams& p, int grid, hipStream_t stream) {
     return hipGetLastError();
 }
 
-template <int OPT>
-hipError_t launch_opt(const StepParams& p, int grid, hipStream_t stream) {
-    if (p.merge) return launch_unfused<OPT>(p, grid, stream);
-    return p.outs ? launch_pull<OPT, true>(p, grid, stream)
-                  : launch_pull<OPT, false>(p, grid, stream);
-}
-
 }  // namespace
 
+// The launchers of one optimizer, with (PULL) and without model buffers.
+// Compiled on its own, this file holds all of them; the library's build
+// compiles it once per launcher (PHUB_STEP_PART = 2 * optimizer + PULL) so
+// that the parts compile side by side, the rest of the file in part 0.
+template <int OPT, bool PULL>
+hipError_t launch_step(const StepParams& p, int grid, hipStream_t stream);
+
+#define PHUB_LAUNCH_STEP(OPT, PULL)                                                      \
+    template <>                                                                          \
+    hipError_t launch_step<OPT, PULL>(const StepParams& p, int grid, hipStream_t stream) { \
+        if constexpr (!PULL)                                                             \
+            if (p.merge) return launch_unfused<OPT>(p, grid, stream);                    \
+        return launch_pull<OPT, PULL>(p, grid, stream);                                  \
+    }
+#if !defined(PHUB_STEP_PART) || PHUB_STEP_PART == 0
+PHUB_LAUNCH_STEP(kOptMomentum, false)
+#endif
+#if !defined(PHUB_STEP_PART) || PHUB_STEP_PART == 1
+PHUB_LAUNCH_STEP(kOptMomentum, true)
+#endif
+#if !defined(PHUB_STEP_PART) || PHUB_STEP_PART == 2
+PHUB_LAUNCH_STEP(kOptNesterov, false)
+#endif
+#if !defined(PHUB_STEP_PART) || PHUB_STEP_PART == 3
+PHUB_LAUNCH_STEP(kOptNesterov, true)
+#endif
+#if !defined(PHUB_STEP_PART) || PHUB_STEP_PART == 4
+PHUB_LAUNCH_STEP(kOptSgd, false)
+#endif
+#if !defined(PHUB_STEP_PART) || PHUB_STEP_PART == 5
+PHUB_LAUNCH_STEP(kOptSgd, true)
+#endif
+#if !defined(PHUB_STEP_PART) || PHUB_STEP_PART == 6
+PHUB_LAUNCH_STEP(kOptAdam, false)
+#endif
+#if !defined(PHUB_STEP_PART) || PHUB_STEP_PART == 7
+PHUB_LAUNCH_STEP(kOptAdam, true)
+#endif
+
+#if !defined(PHUB_STEP_PART) || PHUB_STEP_PART == 0
 namespace {
 
 template <int NW, int S>
@@ -1303,13 +1142,24 @@ hipError_t launch_fused_step(const StepParams& p, int optimizer, int grid, hipSt
     if (p.pool_count > 0 && (p.merge || !takes_tile_pool(p.num_workers, optimizer)))
         return hipErrorInvalidValue;  // only the fixed-N fused kernels walk a pool
     if (!p.merge && !p.heads) return hipErrorInvalidValue;  // the fixed-N kernels read them
+    const bool pull = p.outs && !p.merge;
     switch (optimizer) {
-        case kOptMomentum: return launch_opt<kOptMomentum>(p, grid, stream);
-        case kOptNesterov: return launch_opt<kOptNesterov>(p, grid, stream);
-        case kOptSgd: return launch_opt<kOptSgd>(p, grid, stream);
-        case kOptAdam: return launch_opt<kOptAdam>(p, grid, stream);
+        case kOptMomentum:
+            return pull ? launch_step<kOptMomentum, true>(p, grid, stream)
+                        : launch_step<kOptMomentum, false>(p, grid, stream);
+        case kOptNesterov:
+            return pull ? launch_step<kOptNesterov, true>(p, grid, stream)
+                        : launch_step<kOptNesterov, false>(p, grid, stream);
+        case kOptSgd:
+            return pull ? launch_step<kOptSgd, true>(p, grid, stream)
+                        : launch_step<kOptSgd, false>(p, grid, stream);
+        case kOptAdam:
+            return pull ? launch_step<kOptAdam, true>(p, grid, stream)
+                        : launch_step<kOptAdam, false>(p, grid, stream);
         default: return hipErrorInvalidValue;
     }
 }
+
+#endif  // PHUB_STEP_PART
 
 }  // namespace phub

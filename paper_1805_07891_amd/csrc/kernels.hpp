@@ -261,4 +261,9 @@ void append_wave_heads(const DeviceTables& dt, size_t block, int bins,
 // two bins per wave as described above.  `optimizer` is an OptKind.
 hipError_t launch_fused_step(const StepParams& p, int optimizer, int grid, hipStream_t stream);
 
+// The fused pass of launch_fused_step for worker counts without a fixed-N
+// kernel (no model buffers, no merge buffer, no pool).
+hipError_t launch_fused_step_many(const StepParams& p, int optimizer, int grid,
+                                  hipStream_t stream);
+
 }  // namespace phub

@@ -725,14 +725,23 @@ int phub_init_ex(phub_job** out, int num_workers, int num_keys, const int64_t* k
     // 8-worker jobs 0.77 against 0.76; 25.6 M parameters with 8 workers
     // 0.79 streamed, 0.83 cached while the cache keeps the state from the
     // previous step and 0.75 after the cache was flushed).  Jobs without
-    // bursts (few workers, the any-N kernel, the unfused variant) still gain
-    // from the cache.
+    // bursts (few workers, the unfused variant) still gain from the cache.
     j->num_states = j->opt == phub::kOptSgd ? 1 : j->opt == phub::kOptAdam ? 3 : 2;
     const int64_t elem_state_bytes = j->num_states * int64_t(sizeof(float));
     {
         std::lock_guard<std::mutex> lk(g_live_mu);
         int64_t budget = resident_bytes;
-        const bool stream_all = !unfused && phub::burst_write_back(num_workers, j->num_states);
+        // The any-N kernel bursts too, and measured no slower streamed than
+        // cached at any size, up to 15% faster (25.6 M parameters with 64
+        // workers: 0.844 against 0.73-0.75 of peak): it takes the budget
+        // only where the whole job, gradients included, would fit the cache
+        // (equal there: 0.8 M parameters with 21 workers 13.9 us either way).
+        const bool fits = j->arena_elems <= PHUB_DEVICE_CACHE_BYTES / int64_t(sizeof(float)) /
+                                                (num_workers + j->num_states);
+        const bool stream_all =
+            !unfused && (phub::has_fixed_kernel(num_workers)
+                             ? phub::burst_write_back(num_workers, j->num_states)
+                             : !fits);
         if (budget < 0)
             budget = stream_all ? 0 : std::max<int64_t>(0, PHUB_DEVICE_CACHE_BYTES - g_cache_claimed[j->device]);
         j->resident_elems = std::min(j->arena_elems, budget / elem_state_bytes);

@@ -1,0 +1,97 @@
+"""GPU parity of the kernel for worker counts without a kernel of their own
+(17 and more): every block size and filling of the last block, more workers
+than one load of 64 covers, keys of every remainder class, grids small
+enough that a wave walks many tiles, state cached or streamed or cut inside
+a key; bit-exact against the CPU oracle over two steps."""
+
+import sys
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_1805_07891_amd.job import TorchJob, load_library
+from paper_1805_07891_amd.workloads import Job, key_offsets
+
+pytestmark = pytest.mark.gpu
+
+LR, MU, WD, B1, B2, EPS = 0.05, 0.9, 1e-3, 0.9, 0.999, 1e-8
+STATES = {"sgd": 1, "adam": 3}
+# empty, below a float4, ends of pieces and tiles, several tiles and a ragged end
+KEYS = (0, 1, 3, 4, 7, 255, 256, 257, 1023, 1024, 1030, 5 * 1024 + 513, 2, 1024 * 9)
+
+
+@pytest.fixture(scope="module")
+def torch_dev():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a visible GPU"
+    return torch, torch.device("cuda:0")
+
+
+def _bits_equal(a, b):
+    return np.array_equal(np.asarray(a, np.float32).view(np.uint32),
+                          np.asarray(b, np.float32).view(np.uint32))
+
+
+@pytest.mark.parametrize("n,opt,workgroups,resident", [
+    (17, "nesterov", 1, 0), (17, "momentum", None, None), (18, "sgd", 1, 0), (19, "adam", 1, 0),
+    (21, "nesterov", None, 0), (22, "nesterov", 2, "cut"), (23, "momentum", 1, 0),
+    (25, "adam", None, None), (28, "nesterov", 1, 0), (31, "sgd", None, "cut"),
+    (33, "nesterov", 1, 0), (40, "sgd", 1, 0), (47, "momentum", 2, "cut"), (63, "adam", 1, "cut"),
+    (64, "nesterov", 1, 0), (64, "nesterov", None, None), (65, "nesterov", 1, 0),
+    (130, "momentum", 1, "cut"), (257, "nesterov", None, 0)])
+def test_many_workers(torch_dev, n, opt, workgroups, resident):
+    torch, dev = torch_dev
+    print("many", n, opt, workgroups, resident, flush=True)
+    sys.stdout.flush()
+    states = STATES.get(opt, 2)
+    if resident == "cut":
+        resident = 4 * states * 6000
+    spec = Job("many", n, KEYS, lr=LR, momentum=MU, weight_decay=WD, nesterov=opt == "nesterov")
+    job = TorchJob(spec, dev, lib=load_library(), resident_bytes=resident, workgroups=workgroups,
+                   optimizer={"momentum": None, "nesterov": None}.get(opt, opt), betas=(B1, B2),
+                   eps=EPS)
+    offs, total = key_offsets(KEYS)
+    rng = np.random.default_rng(77 + n)
+
+    def arena(scale):
+        a = np.full(total, np.float32(1e30))  # padding: never read into a result
+        for o, m in zip(offs, KEYS):
+            a[o:o + m] = rng.standard_normal(m, dtype=np.float32) * np.float32(scale)
+        return a.astype(np.float32)
+
+    def split(a):
+        return [a[o:o + m].copy() for o, m in zip(offs, KEYS)]
+
+    w0 = arena(0.05)
+    job.set_weights(torch.from_numpy(w0).to(dev))
+    W, M, V = split(w0), [np.zeros(m, np.float32) for m in KEYS], [np.zeros(m, np.float32) for m in KEYS]
+    for t in range(2):
+        host = [arena(1e-2) for _ in range(n)]
+        if t == 0:
+            for h in host:  # sums of zeros keep their sign
+                h[offs[5]:offs[5] + 64] = -0.0
+        arenas = [torch.from_numpy(a).to(dev) for a in host]
+        for w in range(n):
+            job.attach_grads(w, arenas[w])
+        torch.cuda.synchronize()
+        job.push_and_step()
+        g = [split(h) for h in host]
+        if opt == "sgd":
+            oracle.step_sgd(g, W, LR, WD)
+        elif opt == "adam":
+            oracle.step_adam(g, W, M, V, LR, B1, B2, EPS, WD, t + 1)
+        else:
+            oracle.step(g, W, M, LR, MU, WD, opt == "nesterov")
+        Wg, Mg = job.state_arenas()
+        Vg = job.second_moment_arena()
+        covered = np.zeros(total, bool)
+        for k, (o, m) in enumerate(zip(offs, KEYS)):
+            covered[o:o + m] = True
+            assert _bits_equal(Wg[o:o + m], W[k]), f"step {t}: W key {k}"
+            if opt != "sgd":
+                assert _bits_equal(Mg[o:o + m], M[k]), f"step {t}: M key {k}"
+            if opt == "adam":
+                assert _bits_equal(Vg[o:o + m], V[k]), f"step {t}: V key {k}"
+        assert not Wg[~covered].any(), "padding of W written"
+    job.destroy()
