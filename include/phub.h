@@ -397,9 +397,11 @@ int phub_destroy(phub_job *job);
  * library of 4 MiB (PHUB_NOALLOC_SCRATCH_BYTES), one per GPU, held until
  * the process ends; that bounds a call to about 240 M parameters and
  * PHUB_EINVAL reports a step that does not fit, before anything is
- * enqueued.  The call uploads the schedule on hip_stream after the stream's
- * earlier work and waits for that upload (the host thread blocks until the
- * stream's earlier work is done); the kernel itself runs asynchronously.
+ * enqueued.  The call sends its tables on hip_stream after the stream's
+ * earlier work and builds the schedule on the GPU; the step's kernel runs
+ * asynchronously.  (Only a call with more than about 7600 gradient pointers
+ * and keys waits for its upload, and so for the stream's earlier work.)
+ * A stream that is being captured is refused (PHUB_EHIP).
  * Calls on one GPU share its array: calls that overlap on one GPU (from
  * other threads, or on another stream before this call's kernel has run)
  * race and give wrong results.  All state streams non-temporally (nothing

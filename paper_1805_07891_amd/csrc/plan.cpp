@@ -157,6 +157,27 @@ std::string build_lpt(int num_workers, int num_keys, const int64_t* key_elems,
     return "";
 }
 
+// Items that make_items would cut the keys into.
+int64_t count_items(int num_keys, const int64_t* key_elems, int64_t elems) {
+    int64_t items = 0, bundle_elems = 0;
+    bool open = false;  // the last item is a bundle that can still grow
+    for (int k = 0; k < num_keys; ++k) {
+        const int64_t n = key_elems[k];
+        if (n == 0) continue;
+        if (n >= elems) {
+            items += (n + elems - 1) / elems;
+            open = false;
+        } else if (open && bundle_elems + n <= elems) {
+            bundle_elems += n;
+        } else {
+            ++items;
+            bundle_elems = n;
+            open = true;
+        }
+    }
+    return items;
+}
+
 std::string build_split(int num_workers, int num_keys, const int64_t* key_elems,
                         int64_t chunk_bytes, int num_bins, Plan* out) {
     // Work in float4 slots: key k has ceil(n_k / 4) of them, the last one
@@ -219,6 +240,25 @@ std::string build_plan(int num_workers, int num_keys, const int64_t* key_elems,
     if (schedule == kScheduleLpt)
         return build_lpt(num_workers, num_keys, key_elems, chunk_bytes, num_bins, min_items, out);
     return build_split(num_workers, num_keys, key_elems, chunk_bytes, num_bins, out);
+}
+
+LptCounts lpt_counts(int num_keys, const int64_t* key_elems, int64_t chunk_bytes, int min_items,
+                     int64_t tile_elems) {
+    int64_t elems = chunk_bytes / 4;
+    while (count_items(num_keys, key_elems, elems) < int64_t(min_items) &&
+           elems / 2 >= kMinSplitElems && (elems / 2) % 4 == 0)
+        elems /= 2;
+    LptCounts c;
+    auto add = [&](int64_t segments, int64_t count) {
+        c.tiles += segments * (count / tile_elems);
+        if (count % tile_elems) c.rems += segments;
+    };
+    for (int k = 0; k < num_keys; ++k) {
+        const int64_t n = key_elems[k];
+        if (n >= elems) add(n / elems, elems);
+        add(1, n % elems);  // 0 elements: neither a tile nor a remainder
+    }
+    return c;
 }
 
 }  // namespace phub

@@ -54,4 +54,14 @@ std::string build_plan(int num_workers, int num_keys, const int64_t* key_elems,
                        int64_t chunk_bytes, int schedule, int num_bins, int min_items,
                        Plan* out);
 
+// Full tiles of tile_elems elements and remainders that the LPT schedule's
+// segments would be cut into (the arguments as build_plan's), counted key by
+// key without building the schedule.
+struct LptCounts {
+    int64_t tiles = 0;
+    int64_t rems = 0;
+};
+LptCounts lpt_counts(int num_keys, const int64_t* key_elems, int64_t chunk_bytes, int min_items,
+                     int64_t tile_elems);
+
 }  // namespace phub

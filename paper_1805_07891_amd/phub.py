@@ -261,11 +261,14 @@ class Library:
                           grad_ptrs: Sequence[int], weights_ptr: int, moments_ptr: int,
                           stream: Optional[int] = None, check: bool = True) -> int:
         """One step without allocation over caller arenas (see phub.h);
-        grad_ptrs[w * K + k] is worker w's gradient for key k."""
+        grad_ptrs[w * K + k] is worker w's gradient for key k (a ctypes
+        c_void_p array, see ``pointer_array``, or a sequence of ints)."""
         elems = (ctypes.c_int64 * len(key_elems))(*[int(n) for n in key_elems])
+        if not isinstance(grad_ptrs, ctypes.Array):
+            grad_ptrs = pointer_array(grad_ptrs)
         return self._check(self.lib.phub_step_noalloc(
             int(num_workers), len(key_elems), elems, int(chunk_bytes), float(lr), float(momentum),
-            float(weight_decay), int(bool(nesterov)), pointer_array(grad_ptrs), weights_ptr,
+            float(weight_decay), int(bool(nesterov)), grad_ptrs, weights_ptr,
             moments_ptr, stream), check)
 
     # -- schedule (host only) ----------------------------------------------
