@@ -445,7 +445,10 @@ const char *phub_last_error(void);
  * Item and segment cost is the bytes moved, (N + 4) * 4 per element, plus
  * 4096 per segment.  The result of a step depends on neither schedule nor
  * chunk size.  phub_init uses one bin per wave of its launch (one workgroup
- * of 4 waves per compute unit) and, for LPT, min_items = 32 per bin.
+ * of 4 waves per compute unit).  For LPT it deals the same partition at the
+ * kernels' granularity (full 1024-element tiles in turn, then what is left
+ * over and the keys' ends, largest first to the least loaded wave, small
+ * keys not bundled), except with whole_chunks or chunks below 4096 bytes.
  * ------------------------------------------------------------------------ */
 
 /* One contiguous run of one key handled by one wave. */

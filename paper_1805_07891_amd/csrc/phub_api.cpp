@@ -49,12 +49,12 @@
 #ifndef PHUB_DEVICE_CACHE_BYTES
 #define PHUB_DEVICE_CACHE_BYTES (int64_t(256) << 20)
 #endif
-// The LPT schedule refines chunks until there are this many items per bin
-// (never below 1024 elements).  With ~1000 waves this yields one-tile items
-// for every workload up to ~130 M parameters: the waves then work on
-// neighbouring tiles at any moment, which keeps the window of addresses in
-// flight per array compact (measured: +2.6 points on a 102 M-parameter,
-// 16-worker job over two-tile items).
+// Where the chunks themselves are the LPT schedule's items (chunks below a
+// tile, the dynamic schedule's remainders), they are refined until there are
+// this many per bin (never below 1024 elements): with one-tile items the
+// waves work on neighbouring tiles at any moment, which keeps the window of
+// addresses in flight per array compact (measured: +2.6 points on a 102
+// M-parameter, 16-worker job over two-tile items).
 #ifndef PHUB_LPT_ITEMS_PER_BIN
 #define PHUB_LPT_ITEMS_PER_BIN 128
 #endif
@@ -785,12 +785,28 @@ int phub_init_ex(phub_job** out, int num_workers, int num_keys, const int64_t* k
                     if (!vk.empty()) {
                         std::vector<int64_t> elems(vk.size());
                         for (size_t i = 0; i < vk.size(); ++i) elems[i] = vk[i].elems;
-                        err = phub::build_plan(num_workers, int(vk.size()), elems.data(),
-                                               chunk_bytes,
-                                               schedule == PHUB_SCHEDULE_DYNAMIC ? phub::kScheduleLpt
-                                                                                : schedule,
-                                               bins, whole_chunks ? 0 : kLptItemsPerBin * bins,
-                                               &plan);
+                        // Chunks are divisible here unless the caller says
+                        // otherwise or makes them smaller than a tile.
+                        // Dealt tile by tile against the chunk items'
+                        // bundles (MI355X): 0.25 M parameters in 442 keys,
+                        // 1 worker, Adam 17.1 -> 5.9 us; 0.3 M in 300, 16,
+                        // Adam 26.0 -> 14.2; 0.63 M in 271, 21, Adam 33.9
+                        // -> 19.4; 6.4 M in 40, 8 workers 52.6 -> 50.8;
+                        // 25.6 M in 161, 8 workers 189.4 -> 187.3, 16
+                        // workers 309.9 -> 305.6; others level.
+                        if (schedule == PHUB_SCHEDULE_LPT && !whole_chunks &&
+                            chunk_bytes >= phub::kTileElems * int64_t(sizeof(float)))
+                            err = phub::build_dealt(int(vk.size()), elems.data(), phub::kTileElems,
+                                                    (num_workers + 2 * int64_t(j->num_states)) * 4,
+                                                    bins, &plan);
+                        else
+                            err = phub::build_plan(num_workers, int(vk.size()), elems.data(),
+                                                   chunk_bytes,
+                                                   schedule == PHUB_SCHEDULE_DYNAMIC
+                                                       ? phub::kScheduleLpt
+                                                       : schedule,
+                                                   bins, whole_chunks ? 0 : kLptItemsPerBin * bins,
+                                                   &plan);
                     } else {
                         plan.bin_begin.assign(1, 0);
                     }

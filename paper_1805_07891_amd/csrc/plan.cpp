@@ -242,6 +242,74 @@ std::string build_plan(int num_workers, int num_keys, const int64_t* key_elems,
     return build_split(num_workers, num_keys, key_elems, chunk_bytes, num_bins, out);
 }
 
+std::string build_dealt(int num_keys, const int64_t* key_elems, int64_t tile_elems,
+                        int64_t bytes_per_elem, int num_bins, Plan* out) {
+    if (num_bins < 1) return "num_bins must be >= 1, got " + std::to_string(num_bins);
+    if (tile_elems < 4 * kPieceAlign || tile_elems % kPieceAlign != 0) return "bad tile size";
+    out->segments.clear();
+    out->bin_begin.assign(1, 0);
+    out->bin_cost.clear();
+    out->item_elems = tile_elems;
+    int64_t tiles = 0, rems = 0;
+    for (int k = 0; k < num_keys; ++k) {
+        tiles += key_elems[k] / tile_elems;
+        rems += key_elems[k] % tile_elems != 0;
+    }
+    // Tiles [0, whole) are dealt in turn; the leftover [whole, tiles) is cut
+    // into pieces of `piece` elements, one for each bin that need not take a
+    // remainder, unless a piece would be nearly a tile.
+    int64_t whole = tiles - tiles % num_bins;
+    int64_t piece = 0;
+    if (whole < tiles && rems < num_bins) {
+        const int64_t left = (tiles - whole) * tile_elems, bins = num_bins - rems;
+        piece = (left + bins - 1) / bins;
+        piece = std::max((piece + kPieceAlign - 1) / kPieceAlign * kPieceAlign, 4 * kPieceAlign);
+        if (piece > tile_elems * 3 / 4) piece = 0;
+    }
+    if (piece == 0) whole = tiles;
+
+    std::vector<std::vector<PlanSegment>> per(num_bins);
+    std::vector<int64_t> cost(num_bins, 0);
+    std::vector<PlanSegment> items;  // pieces and remainders
+    int64_t t = 0;
+    for (int k = 0; k < num_keys; ++k) {
+        const int64_t n = key_elems[k], full = n / tile_elems;
+        const int64_t dealt = std::max<int64_t>(0, std::min(full, whole - t));
+        for (int64_t i = 0; i < dealt; ++i) {
+            const int b = int((t + i) % num_bins);
+            per[b].push_back({k, int32_t(tile_elems), i * tile_elems});
+            cost[b] += tile_elems * bytes_per_elem + kSegmentCostBytes;
+        }
+        for (int64_t off = dealt * tile_elems; off < full * tile_elems; off += piece)
+            items.push_back({k, int32_t(std::min(piece, full * tile_elems - off)), off});
+        if (n % tile_elems) items.push_back({k, int32_t(n % tile_elems), full * tile_elems});
+        t += full;
+    }
+    out->num_items = whole + int64_t(items.size());
+    std::stable_sort(items.begin(), items.end(),
+                     [](const PlanSegment& a, const PlanSegment& b) { return a.count > b.count; });
+    using Load = std::pair<int64_t, int>;
+    std::priority_queue<Load, std::vector<Load>, std::greater<Load>> heap;
+    for (int b = 0; b < num_bins; ++b) heap.push({cost[b], b});
+    for (const PlanSegment& s : items) {
+        Load l = heap.top();
+        heap.pop();
+        l.first += s.count * bytes_per_elem + kSegmentCostBytes;
+        cost[l.second] = l.first;
+        per[l.second].push_back(s);
+        heap.push(l);
+    }
+    for (int b = 0; b < num_bins; ++b) {
+        std::sort(per[b].begin(), per[b].end(), [](const PlanSegment& a, const PlanSegment& c) {
+            return a.key != c.key ? a.key < c.key : a.offset < c.offset;
+        });
+        out->segments.insert(out->segments.end(), per[b].begin(), per[b].end());
+        out->bin_begin.push_back(int64_t(out->segments.size()));
+        out->bin_cost.push_back(cost[b]);
+    }
+    return "";
+}
+
 LptCounts lpt_counts(int num_keys, const int64_t* key_elems, int64_t chunk_bytes, int min_items,
                      int64_t tile_elems) {
     int64_t elems = chunk_bytes / 4;

@@ -16,6 +16,10 @@ constexpr int64_t kSegmentCostBytes = 4096;
 // are too few for the bins.
 constexpr int64_t kMinSplitElems = 1024;
 
+// Pieces of a tile that build_dealt cuts are a multiple of this many
+// elements (256 bytes of every array), and at least four times that.
+constexpr int64_t kPieceAlign = 64;
+
 constexpr int kMaxWorkers = 4096;
 constexpr int64_t kMaxKeyElems = int64_t(1) << 40;
 constexpr int64_t kMaxChunkBytes = int64_t(1) << 30;
@@ -53,6 +57,20 @@ std::string validate_shape(int num_workers, int num_keys, const int64_t* key_ele
 std::string build_plan(int num_workers, int num_keys, const int64_t* key_elems,
                        int64_t chunk_bytes, int schedule, int num_bins, int min_items,
                        Plan* out);
+
+// The schedule that phub_init runs for PHUB_SCHEDULE_LPT (kept apart from
+// build_plan, whose schedule is part of the interface): the same balanced
+// partition, dealt at the granularity the kernels work in.  Every key's full
+// tiles of tile_elems elements go to the bins in turn (which is what the
+// longest-processing-time-first rule does with equal items), the leftover of
+// the last round and the keys' remainders largest first to the least loaded
+// bin.  Where few enough tiles are left over, they are cut into equal pieces
+// so that every bin gets one, and small keys are not bundled: on a job of a
+// few tiles per wave the last round is a large part of the launch, and a
+// wave walks its remainders one after another.  bytes_per_elem: what the
+// step moves per element.
+std::string build_dealt(int num_keys, const int64_t* key_elems, int64_t tile_elems,
+                        int64_t bytes_per_elem, int num_bins, Plan* out);
 
 // Full tiles of tile_elems elements and remainders that the LPT schedule's
 // segments would be cut into (the arguments as build_plan's), counted key by
