@@ -268,18 +268,12 @@ std::string build_dealt(int num_keys, const int64_t* key_elems, int64_t tile_ele
     }
     if (piece == 0) whole = tiles;
 
-    std::vector<std::vector<PlanSegment>> per(num_bins);
-    std::vector<int64_t> cost(num_bins, 0);
-    std::vector<PlanSegment> items;  // pieces and remainders
+    // the pieces and remainders, largest first
+    std::vector<PlanSegment> items;
     int64_t t = 0;
     for (int k = 0; k < num_keys; ++k) {
         const int64_t n = key_elems[k], full = n / tile_elems;
         const int64_t dealt = std::max<int64_t>(0, std::min(full, whole - t));
-        for (int64_t i = 0; i < dealt; ++i) {
-            const int b = int((t + i) % num_bins);
-            per[b].push_back({k, int32_t(tile_elems), i * tile_elems});
-            cost[b] += tile_elems * bytes_per_elem + kSegmentCostBytes;
-        }
         for (int64_t off = dealt * tile_elems; off < full * tile_elems; off += piece)
             items.push_back({k, int32_t(std::min(piece, full * tile_elems - off)), off});
         if (n % tile_elems) items.push_back({k, int32_t(n % tile_elems), full * tile_elems});
@@ -288,25 +282,56 @@ std::string build_dealt(int num_keys, const int64_t* key_elems, int64_t tile_ele
     out->num_items = whole + int64_t(items.size());
     std::stable_sort(items.begin(), items.end(),
                      [](const PlanSegment& a, const PlanSegment& b) { return a.count > b.count; });
-    using Load = std::pair<int64_t, int>;
-    std::priority_queue<Load, std::vector<Load>, std::greater<Load>> heap;
-    for (int b = 0; b < num_bins; ++b) heap.push({cost[b], b});
-    for (const PlanSegment& s : items) {
-        Load l = heap.top();
-        heap.pop();
-        l.first += s.count * bytes_per_elem + kSegmentCostBytes;
-        cost[l.second] = l.first;
-        per[l.second].push_back(s);
-        heap.push(l);
-    }
+
+    // each to the least loaded bin, lowest index on ties
+    const int64_t tile_cost = tile_elems * bytes_per_elem + kSegmentCostBytes;
+    std::vector<int64_t> cost(num_bins);
+    std::vector<int64_t> size(num_bins);  // segments of each bin
     for (int b = 0; b < num_bins; ++b) {
-        std::sort(per[b].begin(), per[b].end(), [](const PlanSegment& a, const PlanSegment& c) {
-            return a.key != c.key ? a.key < c.key : a.offset < c.offset;
-        });
-        out->segments.insert(out->segments.end(), per[b].begin(), per[b].end());
-        out->bin_begin.push_back(int64_t(out->segments.size()));
+        size[b] = whole / num_bins + (b < whole % num_bins ? 1 : 0);
+        cost[b] = size[b] * tile_cost;
+    }
+    std::vector<int> owner(items.size());
+    if (!items.empty()) {
+        using Load = std::pair<int64_t, int>;
+        std::vector<Load> loads(num_bins);
+        for (int b = 0; b < num_bins; ++b) loads[b] = {cost[b], b};
+        std::priority_queue<Load, std::vector<Load>, std::greater<Load>> heap(
+            std::greater<Load>(), std::move(loads));
+        for (size_t i = 0; i < items.size(); ++i) {
+            Load l = heap.top();
+            heap.pop();
+            owner[i] = l.second;
+            l.first += items[i].count * bytes_per_elem + kSegmentCostBytes;
+            cost[l.second] = l.first;
+            ++size[l.second];
+            heap.push(l);
+        }
+    }
+
+    // each bin's tiles, then its items, then in key and offset order
+    std::vector<int64_t> at(num_bins);
+    int64_t total = 0;
+    for (int b = 0; b < num_bins; ++b) {
+        at[b] = total;
+        total += size[b];
+        out->bin_begin.push_back(total);
         out->bin_cost.push_back(cost[b]);
     }
+    out->segments.resize(size_t(total));
+    t = 0;
+    for (int k = 0; k < num_keys && t < whole; ++k) {
+        const int64_t full = key_elems[k] / tile_elems;
+        for (int64_t i = 0; i < full && t < whole; ++i, ++t)
+            out->segments[at[t % num_bins]++] = {k, int32_t(tile_elems), i * tile_elems};
+    }
+    for (size_t i = 0; i < items.size(); ++i) out->segments[at[owner[i]]++] = items[i];
+    for (int b = 0; b < num_bins && !items.empty(); ++b)
+        std::sort(out->segments.begin() + out->bin_begin[b],
+                  out->segments.begin() + out->bin_begin[b + 1],
+                  [](const PlanSegment& x, const PlanSegment& y) {
+                      return x.key != y.key ? x.key < y.key : x.offset < y.offset;
+                  });
     return "";
 }
 
