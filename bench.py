@@ -37,7 +37,10 @@ HBM_PEAK_GBS = 8000.0
 # Sources that decide what the measured kernel reads and writes: the kernel
 # itself and the host code that builds its schedule and tables.
 KERNEL_SOURCES = ["paper_1805_07891_amd/csrc/fused_step.hip",
+                  "paper_1805_07891_amd/csrc/fused_stream.hip",
                   "paper_1805_07891_amd/csrc/fused_many.hip",
+                  "paper_1805_07891_amd/csrc/tile_walk.hpp",
+                  "paper_1805_07891_amd/csrc/stream_walk.hpp",
                   "paper_1805_07891_amd/csrc/device.hpp", "paper_1805_07891_amd/csrc/kernels.hpp",
                   "paper_1805_07891_amd/csrc/plan.cpp", "paper_1805_07891_amd/csrc/plan.hpp",
                   "paper_1805_07891_amd/csrc/phub_api.cpp"]

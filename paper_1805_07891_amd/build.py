@@ -27,10 +27,12 @@ PROBE_LIB = os.path.join(PKG, "libphub_probe.so")
 GRADIENTS_CACHED_LIB = os.path.join(PKG, "libphub_gradients_cached.so")
 PROBE_SOURCES = ["probe.hip"]
 
-SOURCES = ["plan.cpp", "phub_api.cpp", "fused_step.hip", "fused_many.hip", "step_noalloc.hip"]
-HEADERS = ["plan.hpp", "kernels.hpp", "device.hpp"]
-# fused_step.hip holds hundreds of kernels: it is compiled in this many parts
-STEP_PARTS = 8
+SOURCES = ["plan.cpp", "phub_api.cpp", "fused_step.hip", "fused_stream.hip", "fused_many.hip",
+           "step_noalloc.hip"]
+HEADERS = ["plan.hpp", "kernels.hpp", "device.hpp", "tile_walk.hpp", "stream_walk.hpp"]
+# Sources that hold many kernels, and the parts (PHUB_STEP_PART) that they are
+# compiled in
+PARTS = {"fused_step.hip": range(8), "fused_stream.hip": range(0, 8, 2)}
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
@@ -54,9 +56,8 @@ def build(out: str = LIB, defines: Sequence[str] = (), extra: Sequence[str] = ()
     path.  ``defines`` are extra -D settings (used for launch-shape sweeps)."""
     flags = [f for f in FLAGS if f != "-shared"]
     units = []  # (source, its own defines), the longest compilations first
-    for s in sorted(SOURCES, key=lambda s: s != "fused_step.hip"):
-        parts = range(STEP_PARTS) if s == "fused_step.hip" else (None,)
-        units += [(s, [] if p is None else [f"PHUB_STEP_PART={p}"]) for p in parts]
+    for s in sorted(SOURCES, key=lambda s: s not in PARTS):
+        units += [(s, [] if p is None else [f"PHUB_STEP_PART={p}"]) for p in PARTS.get(s, (None,))]
     with tempfile.TemporaryDirectory(dir=os.path.dirname(os.path.abspath(out))) as tmp:
         def compile_one(i: int) -> str:
             src, own = units[i]

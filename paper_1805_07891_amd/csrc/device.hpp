@@ -22,12 +22,17 @@ constexpr int kWavesPerBlock = kBlockThreads / 64;
 template <int OPT>
 constexpr int kStates = OPT == kOptSgd ? 1 : (OPT == kOptAdam ? 3 : 2);
 
-// Correctly rounded single-precision square root.  The hardware square
-// root (with the compiler's denormal scaling) is within one ulp, so the
-// correctly rounded root is y, or its neighbour below or above.  The
-// midpoints between neighbours have at most 25 significant bits, so their
-// squares are exact in double; comparing x with them decides exactly
-// (a float's square root is never a midpoint, so there are no ties).
+// Correctly rounded single-precision square root, with the rounding checked
+// in double: the hardware root is within one ulp, the midpoints between
+// neighbours have at most 25 significant bits, so their squares are exact in
+// double and comparing x with them decides (a float's square root is never
+// a midpoint, so there are no ties).  The compiler's own sequence for
+// __builtin_sqrtf gives the same bits for all 2^32 inputs, in half the
+// instructions.  The streamed walk uses that (Adam with 16 and 33 workers
+// +2.8 and +0.7 points); the piece-by-piece walks, whose load windows were
+// tuned with the longer one, ran 0.3 to 3.6 points below without it (1 to 6
+// workers, nothing cached, also with windows of 4, 6, 8 and 12 loads but
+// for 3 and 4 workers), so they keep it.
 __device__ __forceinline__ float sqrt_rn(float x) {
     const float y = __builtin_sqrtf(x);
     if (!(x > 0.0f) || !(y < __builtin_huge_valf())) return y;  // 0, < 0, NaN, inf
@@ -42,8 +47,9 @@ __device__ __forceinline__ float sqrt_rn(float x) {
     return y;
 }
 
-// One element: st[0] = w, st[1] = m, st[2] = v, updated in place.
-template <int OPT>
+// One element: st[0] = w, st[1] = m, st[2] = v, updated in place.  CHECKED:
+// with sqrt_rn's check (the same result either way).
+template <int OPT, bool CHECKED = true>
 __device__ __forceinline__ void update(float s, float* st, OptArgs o) {
     if constexpr (OPT == kOptSgd) {
         const float d = __builtin_fmaf(o.wd, st[0], s);
@@ -53,7 +59,8 @@ __device__ __forceinline__ void update(float s, float* st, OptArgs o) {
         const float m = __builtin_fmaf(o.b1, st[1], o.c1 * d);
         const float dd = d * d;
         const float v = __builtin_fmaf(o.b2, st[2], o.c2 * dd);
-        const float den = sqrt_rn(v * o.k2) + o.eps;
+        const float root = CHECKED ? sqrt_rn(v * o.k2) : __builtin_sqrtf(v * o.k2);
+        const float den = root + o.eps;
         const float q = __fdiv_rn(o.k1 * m, den);
         st[0] = st[0] - q;
         st[1] = m;
@@ -69,14 +76,14 @@ __device__ __forceinline__ void update(float s, float* st, OptArgs o) {
 }
 
 // Four elements at once (a float4 of each array).
-template <int OPT>
+template <int OPT, bool CHECKED = true>
 __device__ __forceinline__ void update4(const f4& s, f4* st, OptArgs o) {
     if constexpr (OPT == kOptAdam) {
         // the square root and division per component, correctly rounded
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             float e[3] = {st[0][c], st[1][c], st[2][c]};
-            update<OPT>(s[c], e, o);
+            update<OPT, CHECKED>(s[c], e, o);
             st[0][c] = e[0];
             st[1][c] = e[1];
             st[2][c] = e[2];

@@ -195,6 +195,7 @@ struct StepParams {
     const DevRem* rems;           // grouped by bin
     const int32_t* rem_begin;     // 2 * bins + 1 offsets into rems
     const WaveHead* heads;        // one per wave (the fixed-N kernels read these, not the offsets)
+    int64_t streamed_tiles;       // full tiles of all streamed bins
     const float* const* grads;    // [row * num_workers + worker], 16-byte aligned
     float* const* outs;           // same layout: model buffers that receive w' (pushpull), or null
     float* merge;                 // unfused ablation: sum buffer laid out like W, or null (fused)
@@ -261,9 +262,49 @@ void append_wave_heads(const DeviceTables& dt, size_t block, int bins,
 // two bins per wave as described above.  `optimizer` is an OptKind.
 hipError_t launch_fused_step(const StepParams& p, int optimizer, int grid, hipStream_t stream);
 
+// Loads per block where a step's streamed tiles are walked as one stream of
+// load blocks (stream_walk.hpp), 5 or 6; 0: the fixed-N kernels' window over
+// a tile is faster.  Measured on MI355X with nothing cached, 25.6 and 61.1 M
+// parameters, fraction of peak, window over a tile -> stream (the better of
+// the two blocks):
+//   momentum  8 workers 0.827 -> 0.842, 9 0.827 -> 0.849, 13 0.834 -> 0.838,
+//             14 0.837 -> 0.852, 15 0.837 -> 0.856, 16 0.838 -> 0.850,
+//             20 0.845 -> 0.865, 24 0.847 -> 0.854, 32 0.837 -> 0.868, 10
+//             +0.2 to +0.7 points; 7, 11 and 12 0.4 to 1.4 points below
+//   SGD       9 0.839 -> 0.853, 10 0.845 -> 0.867, 11 0.851 -> 0.857, 15
+//             0.851 -> 0.865, 16 0.852 -> 0.872, 24 0.860 -> 0.870, 32 0.859
+//             -> 0.867; 7, 8 and 12 0.3 to 1 point below, 13 and 14 level
+//   Adam      7 0.768 -> 0.790, 8 0.757 -> 0.806, 10 0.720 -> 0.791, 12 0.747
+//             -> 0.811, 14 0.784 -> 0.825, 16 0.773 -> 0.819, 32 0.798 ->
+//             0.846
+// With 6 workers and fewer a piece would be a single block.
+constexpr int kStreamBlock[3][kMaxFixedWorkers] = {
+    {0, 0, 0, 0, 0, 0, 0, 0, 5, 5, 6, 0, 0, 0, 6, 6},
+    {0, 0, 0, 0, 0, 0, 0, 5, 5, 6, 0, 0, 6, 5, 6, 6},
+    {0, 0, 0, 0, 0, 0, 5, 5, 6, 5, 5, 5, 6, 5, 6, 6},
+};
+
+// Fewest streamed tiles per wave for that: the stream starts slower (a
+// descriptor, then pointers, then data, where the other kernels' first
+// descriptors come with the head).  Stream against window over a tile at 2,
+// 3, 4, 5, 6 and 8 tiles per wave: momentum with 8 workers -1.8, -1.6, 0.0,
+// -0.1, +1.1, +0.3 points, 16 workers +0.6, +0.3, -0.7, +1.0, +0.3, +1.4;
+// SGD with 10 -0.3, +0.9, +0.4, +1.3, +2.2, +2.3; Adam with 8 +1.5, +1.9,
+// +2.9, +4.9, +3.9, +3.9; below one tile 4 to 12 points down (momentum).
+constexpr int kStreamMinTiles[3] = {4, 4, 2};
+
+constexpr int stream_block(int num_workers, int num_states) {
+    return num_workers > kMaxFixedWorkers ? 6 : kStreamBlock[num_states - 1][num_workers - 1];
+}
+
 // The fused pass of launch_fused_step for worker counts without a fixed-N
 // kernel (no model buffers, no merge buffer, no pool).
 hipError_t launch_fused_step_many(const StepParams& p, int optimizer, int grid,
                                   hipStream_t stream);
+
+// The same for worker counts with a fixed-N kernel where stream_block is not
+// 0 (OPT an OptKind).
+template <int OPT>
+hipError_t launch_stream(const StepParams& p, int grid, hipStream_t stream);
 
 }  // namespace phub

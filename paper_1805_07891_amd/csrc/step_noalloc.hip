@@ -388,6 +388,7 @@ extern "C" int phub_step_noalloc(int num_workers, int num_keys, const int64_t* k
 
     phub::StepParams p{};
     p.heads = d_heads;
+    p.streamed_tiles = num_tiles;
     p.tiles = d_tiles;
     p.rems = d_rems;
     p.grads = reinterpret_cast<const float* const*>(d_ptrs);
