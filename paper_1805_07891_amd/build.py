@@ -28,7 +28,7 @@ GRADIENTS_CACHED_LIB = os.path.join(PKG, "libphub_gradients_cached.so")
 PROBE_SOURCES = ["probe.hip"]
 
 SOURCES = ["plan.cpp", "phub_api.cpp", "fused_step.hip", "fused_stream.hip", "fused_many.hip",
-           "step_noalloc.hip"]
+           "put_pointers.hip", "step_noalloc.hip"]
 HEADERS = ["plan.hpp", "kernels.hpp", "device.hpp", "tile_walk.hpp", "stream_walk.hpp"]
 # Sources that hold many kernels, and the parts (PHUB_STEP_PART) that they are
 # compiled in

@@ -307,4 +307,12 @@ hipError_t launch_fused_step_many(const StepParams& p, int optimizer, int grid,
 template <int OPT>
 hipError_t launch_stream(const StepParams& p, int grid, hipStream_t stream);
 
+// Enqueues the writing of up to kPutPointers pointers to the device address
+// dst as the arguments of one launch (`pointers` may change once it
+// returns); false, with nothing enqueued, where there are more or one does
+// not fit 48 bits.
+constexpr int kPutPointers = 640;
+bool put_pointers(const void* const* pointers, size_t count, void* dst, hipStream_t stream,
+                  hipError_t* error);
+
 }  // namespace phub

@@ -259,10 +259,17 @@ int claim_stage(phub_job* j) {
     return PHUB_OK;
 }
 
-// Copies rows [r0, r1) of a host pointer table to the device, through the
-// current step's staging slot, on the job's stream.
+// Copies entries [r0, r1) of a host pointer table to the device, on the
+// job's stream: a small table as kernel arguments, others through the
+// current step's staging slot.
 template <typename T>
 int upload_range(phub_job* j, T* const* host, T** stage, T** dev, size_t r0, size_t r1) {
+    hipError_t put = hipSuccess;
+    if (r1 > r0 && phub::put_pointers(reinterpret_cast<const void* const*>(host + r0), r1 - r0,
+                                      dev + r0, j->stream, &put)) {
+        if (put != hipSuccess) return hip_fail(put, "launch of the pointer upload");
+        return PHUB_OK;
+    }
     if (int rc = claim_stage(j)) return rc;
     if (r1 > r0) {
         const int slot = j->stage_slot;
