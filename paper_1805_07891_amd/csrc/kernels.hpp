@@ -120,13 +120,16 @@ constexpr int stash_tiles(int num_states) {
 // kWritePeriodNsPerStreamTile per element stream of a tile (N + 2 S
 // streams: gradients, state read, state written) and stashed tile; the
 // window is about one tile (kWriteWindowNs).  The host converts both to
-// clock ticks.  Swept on MI355X with momentum at 8 and 16 workers: 550-700
-// ns per stream and tile and 6-10 us windows lie within a point of each
-// other, 800 ns with a 15.4 us window 1-2.6 points below; a period of
-// four tiles for every optimizer measured 1.5-2.7 points below this for
-// plain SGD at 8 workers and 1.8 below for Adam at 16.
-constexpr int64_t kWritePeriodNsPerStreamTile = 650;
-constexpr int64_t kWriteWindowNs = 8000;
+// clock ticks.  By state arrays (plain SGD, momentum, Adam), so that a
+// period is about 0.93 of the time a wave takes to fill its stash.  Swept
+// on MI355X: momentum at 8 and 16 workers, 550-700 ns per stream and tile
+// and 6-10 us windows lie within a point of each other, 800 ns with a 15.4
+// us window 1-2.6 points below; plain SGD, 650 -> 600 ns at 6 to 64 workers
+// +0.3 to +0.9 points (8 over 61.1 M parameters 0.834 -> 0.841); Adam, 650
+// ns and 8 us -> 800 and 7 at 7 to 64 workers +0.1 to +1.7 points (8 over
+// 61.1 M 0.809 -> 0.819).
+constexpr int64_t kWritePeriodNsPerStreamTile[3] = {600, 650, 800};
+constexpr int64_t kWriteWindowNs[3] = {8000, 8000, 7000};
 
 // Write-phase period and window of the burst write-back in ticks of a wall
 // clock running at clock_khz, for a job with num_workers gradients and
@@ -135,8 +138,8 @@ inline void write_phase_ticks(int num_workers, int num_states, int64_t clock_khz
                               uint32_t* period, uint32_t* window) {
     const int64_t streams = num_workers + 2 * int64_t(num_states);
     const int64_t tiles = std::max<int64_t>(stash_tiles(num_states) - 1, 1);
-    const int64_t p = kWritePeriodNsPerStreamTile * streams * tiles * clock_khz / 1000000;
-    const int64_t w = kWriteWindowNs * clock_khz / 1000000;
+    const int64_t p = kWritePeriodNsPerStreamTile[num_states - 1] * streams * tiles * clock_khz / 1000000;
+    const int64_t w = kWriteWindowNs[num_states - 1] * clock_khz / 1000000;
     *period = uint32_t(std::min<int64_t>(std::max<int64_t>(p, 2), INT32_MAX));
     *window = uint32_t(std::min<int64_t>(std::max<int64_t>(w, 1), *period - 1));
 }
