@@ -904,9 +904,8 @@ def measure(torch, dev, lib, wl, args, cpu_seconds: float, streams, helper) -> d
                else measured_traffic(wl.name))
     groups, threads, segs, _, _ = jobs[dom].info()
     cached = [job.cached_fraction() for job in jobs]
-    n_any = any(not (s.num_workers <= 16 or s.num_workers in (20, 24, 32)) for s in wl.jobs)
     kernel = ("aggregate_only + optimize_only" if args.unfused else
-              "fused_step_any" if n_any else "fused_step_fixed")
+              "fused_step (fixed, stream or many: the library's choice)")
     if len(jobs) > 1:
         kernel += (f" x{len(jobs)} (one launch per job, " +
                    ("taking turns on one stream)" if shared_stream else "concurrent on their own streams)"))
