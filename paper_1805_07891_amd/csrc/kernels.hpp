@@ -103,6 +103,20 @@ constexpr bool burst_write_back(int num_workers, int num_states) {
            num_workers >= kBurstMinWorkers[num_states - 1];
 }
 
+// Whether the full tiles left over from the last whole round of a dealt
+// schedule (build_dealt) are cut evenly over the waves: only where their
+// state is streamed and written back in bursts.  Measured on MI355X, whole
+// -> cut: 8 workers over 1.2 M parameters 12.2 -> 10.8 us, over 4.7 M 39.3
+// -> 37.4, 16 over 2.4 M 34.7 -> 32.4, pushpull with 8 over 1.2 M 23.0 ->
+// 20.7.  The other kernels run a second tile on in the load window of the
+// first, and a piece costs its own trip to memory: 2 workers over 1.2 M 6.8
+// -> 7.6 us, 4 over 1.2 M 8.3 -> 9.1, Adam with 8 over 1.7 M 19.4 -> 20.4, 17
+// over 1.4 M 23.2 -> 24.4, cached state with 8 over 1.2 M 11.4 -> 12.5; four
+// jobs at once up to 25% (1 worker, Adam, 1.7 M each 37 -> 46).
+constexpr bool cuts_leftover(int num_workers, int num_states, bool streamed, bool unfused) {
+    return streamed && !unfused && burst_write_back(num_workers, num_states);
+}
+
 // The burst write-back's stash: LDS per wave (the compute unit's 160 KB
 // over its four waves), and how many tiles of state it holds for a job
 // with num_states state arrays (a tile is 4 KB per array and wave).

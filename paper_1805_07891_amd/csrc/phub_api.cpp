@@ -807,7 +807,9 @@ int phub_init_ex(phub_job** out, int num_workers, int num_keys, const int64_t* k
                             chunk_bytes >= phub::kTileElems * int64_t(sizeof(float)))
                             err = phub::build_dealt(int(vk.size()), elems.data(), phub::kTileElems,
                                                     (num_workers + 2 * int64_t(j->num_states)) * 4,
-                                                    bins, &plan);
+                                                    bins, &plan,
+                                                    phub::cuts_leftover(num_workers, j->num_states,
+                                                                        ph == 1, unfused));
                         else
                             err = phub::build_plan(num_workers, int(vk.size()), elems.data(),
                                                    chunk_bytes,

@@ -62,15 +62,15 @@ std::string build_plan(int num_workers, int num_keys, const int64_t* key_elems,
 // build_plan, whose schedule is part of the interface): the same balanced
 // partition, dealt at the granularity the kernels work in.  Every key's full
 // tiles of tile_elems elements go to the bins in turn (which is what the
-// longest-processing-time-first rule does with equal items), the leftover of
-// the last round and the keys' remainders largest first to the least loaded
-// bin.  Where few enough tiles are left over, they are cut into equal pieces
-// so that every bin gets one, and small keys are not bundled: on a job of a
-// few tiles per wave the last round is a large part of the launch, and a
-// wave walks its remainders one after another.  bytes_per_elem: what the
-// step moves per element.
+// longest-processing-time-first rule does with equal items), then the keys'
+// remainders largest first to the least loaded bin; small keys are not
+// bundled (a wave walks its remainders one after another).  cut_leftover:
+// where there is a whole round of tiles and few enough are left over, those
+// are cut into equal pieces so that every bin gets one.  bytes_per_elem:
+// what the step moves per element.
 std::string build_dealt(int num_keys, const int64_t* key_elems, int64_t tile_elems,
-                        int64_t bytes_per_elem, int num_bins, Plan* out);
+                        int64_t bytes_per_elem, int num_bins, Plan* out,
+                        bool cut_leftover = true);
 
 // Full tiles of tile_elems elements and remainders that the LPT schedule's
 // segments would be cut into (the arguments as build_plan's), counted key by
