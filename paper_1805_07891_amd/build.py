@@ -89,12 +89,13 @@ def build_probe(out: str = PROBE_LIB, verbose: bool = False) -> str:
     return out
 
 
-def device_assembly(out: str, source: str = "fused_step.hip") -> str:
+def device_assembly(out: str, source: str = "fused_step.hip", defines: Sequence[str] = ()) -> str:
     """Compile one HIP source of the library to gfx950 device assembly (with
     its kernel metadata: registers, LDS, scratch, spills) at ``out``; the
-    code-generation tests read it."""
+    code-generation tests read it.  ``defines`` as ``build``'s."""
     flags = [f for f in FLAGS if f not in ("-fPIC", "-shared")]
-    cmd = [HIPCC, *flags, f"-I{INCLUDE}", f"-I{CSRC}", "--cuda-device-only", "-S",
+    cmd = [HIPCC, *flags, f"-I{INCLUDE}", f"-I{CSRC}", *[f"-D{d}" for d in defines],
+           "--cuda-device-only", "-S",
            os.path.join(CSRC, source), "-o", out]
     subprocess.check_call(cmd, stderr=subprocess.DEVNULL)
     return out

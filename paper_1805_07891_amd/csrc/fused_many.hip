@@ -40,7 +40,7 @@ namespace phub {
 namespace {
 
 // Loads of a block, and in flight.
-constexpr int B = 6;
+constexpr int B = kManyBlock;
 static_assert(kMaxFixedWorkers >= B, "every piece takes at least two blocks");
 
 // The last 1-3 elements of each remainder of a bin.  Lane 4 k + e of a load

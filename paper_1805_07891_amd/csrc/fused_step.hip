@@ -105,9 +105,10 @@ __global__ __launch_bounds__(kBlockThreads) PHUB_ONE_WAVE_PER_SIMD void fused_st
                                     h.first_rem_streamed, grads, outs, state, o);
 }
 
-// Pushpull with any N (fused_many.hip has the other steps): workers taken in
-// batches of kBatch, each batch's loads in flight together, the running sum
-// carried across batches in worker order.
+// Any N, the worker count a run-time number: workers taken in batches of
+// kBatch, each batch's loads in flight together, the running sum carried
+// across batches in worker order.  It takes the pushpull steps, and the other
+// steps where any_kernel (kernels.hpp) says so; fused_many.hip has the rest.
 constexpr int kBatch = 8;
 
 __device__ __forceinline__ f4 sum_any(const float* const* kp, int n, int64_t offset,
@@ -149,7 +150,7 @@ __device__ __forceinline__ void sum_any_pieces(const float* const* kp, int n, in
     }
 }
 
-template <int OPT, bool RES>
+template <int OPT, bool RES, bool PULL>
 __device__ __forceinline__ void run_any(const float* const* kp, float* const* ko, int n,
                                         int64_t offset, float* const* stb, uint32_t nvec,
                                         uint32_t rem, OptArgs o) {
@@ -171,7 +172,8 @@ __device__ __forceinline__ void run_any(const float* const* kp, float* const* ko
             update4<OPT>(sum[u], st[u], o);
 #pragma unroll
             for (int i = 0; i < S; ++i) store_wm<RES>(stb[i], bo + u * 1024u, st[u][i]);
-            for (int w = 0; w < n; ++w) store_out(ko[w] + offset, bo + u * 1024u, st[u][0]);
+            if constexpr (PULL)
+                for (int w = 0; w < n; ++w) store_out(ko[w] + offset, bo + u * 1024u, st[u][0]);
         }
     }
     for (uint32_t v = nfull + lane; v < nvec; v += 64u) {
@@ -183,7 +185,8 @@ __device__ __forceinline__ void run_any(const float* const* kp, float* const* ko
         update4<OPT>(s, st, o);
 #pragma unroll
         for (int i = 0; i < S; ++i) store_wm<RES>(stb[i], bo, st[i]);
-        for (int w = 0; w < n; ++w) store_out(ko[w] + offset, bo, st[0]);
+        if constexpr (PULL)
+            for (int w = 0; w < n; ++w) store_out(ko[w] + offset, bo, st[0]);
     }
     if (lane < rem) {
         const int64_t i = int64_t(nvec) * 4 + lane;
@@ -195,12 +198,13 @@ __device__ __forceinline__ void run_any(const float* const* kp, float* const* ko
         update<OPT>(s, st, o);
 #pragma unroll
         for (int k = 0; k < S; ++k) store1(stb[k], i, st[k]);
-        for (int w = 0; w < n; ++w) store1(ko[w] + offset, i, st[0]);
+        if constexpr (PULL)
+            for (int w = 0; w < n; ++w) store1(ko[w] + offset, i, st[0]);
     }
 }
 
 // One bin of the any-N kernel: full tiles [tb, te), then remainders [rb, re).
-template <int OPT, bool RES>
+template <int OPT, bool RES, bool PULL>
 __device__ __forceinline__ void any_bin(const DevTile* __restrict__ tiles, int32_t tb, int32_t te,
                                         const DevRem* __restrict__ rems, int32_t rb, int32_t re,
                                         const float* const* __restrict__ grads,
@@ -212,29 +216,34 @@ __device__ __forceinline__ void any_bin(const DevTile* __restrict__ tiles, int32
         float* stb[S];
 #pragma unroll
         for (int i = 0; i < S; ++i) stb[i] = state[i] + tl.arena_offset;
-        run_any<OPT, RES>(grads + int64_t(tl.key) * n, outs + int64_t(tl.key) * n, n,
-                          int64_t(tl.vec) * 4, stb, uint32_t(kTileElems / 4), 0u, o);
+        run_any<OPT, RES, PULL>(grads + int64_t(tl.key) * n,
+                                PULL ? outs + int64_t(tl.key) * n : nullptr, n,
+                                int64_t(tl.vec) * 4, stb, uint32_t(kTileElems / 4), 0u, o);
     }
     for (int32_t r = rb; r < re; ++r) {
         const DevRem rm = rems[r];
         float* stb[S];
 #pragma unroll
         for (int i = 0; i < S; ++i) stb[i] = state[i] + rm.arena_offset;
-        run_any<OPT, RES>(grads + int64_t(rm.key) * n, outs + int64_t(rm.key) * n, n, rm.offset,
-                          stb, uint32_t(rm.count) >> 2, uint32_t(rm.count) & 3u, o);
+        run_any<OPT, RES, PULL>(grads + int64_t(rm.key) * n,
+                                PULL ? outs + int64_t(rm.key) * n : nullptr, n, rm.offset, stb,
+                                uint32_t(rm.count) >> 2, uint32_t(rm.count) & 3u, o);
     }
 }
 
-template <int OPT>
+// (A launch built on the device has heads but no bin offsets, so the bins are
+// read from the heads.)
+template <int OPT, bool PULL>
 __global__ __launch_bounds__(kBlockThreads) void fused_step_any(PHUB_KERNEL_ARGS) {
     float* const state[3] = {weights, moments, second};
     const uint32_t wave = wave_index();
-    const uint32_t bins = gridDim.x * kWavesPerBlock;
-    any_bin<OPT, false>(tiles, tile_begin[bins + wave], tile_begin[bins + wave + 1], rems,
-                        rem_begin[bins + wave], rem_begin[bins + wave + 1], grads, outs, state,
-                        num_workers, o);
-    any_bin<OPT, true>(tiles, tile_begin[wave], tile_begin[wave + 1], rems, rem_begin[wave],
-                       rem_begin[wave + 1], grads, outs, state, num_workers, o);
+    const WaveHead h = heads[wave];
+    any_bin<OPT, false, PULL>(tiles, h.tiles_streamed[0], h.tiles_streamed[1], rems,
+                              h.rems_streamed[0], h.rems_streamed[1], grads, outs, state,
+                              num_workers, o);
+    any_bin<OPT, true, PULL>(tiles, h.tiles_resident[0], h.tiles_resident[1], rems,
+                             h.rems_resident[0], h.rems_resident[1], grads, outs, state,
+                             num_workers, o);
 }
 
 // Ablation: the unfused ("wide") form of the step, kept to measure what
@@ -343,15 +352,16 @@ __global__ __launch_bounds__(kBlockThreads) void optimize_only(PHUB_KERNEL_ARGS,
 
 template <int OPT, bool PULL>
 hipError_t launch_any(const StepParams& p, int grid, hipStream_t stream) {
-    if constexpr (PULL) {
-        hipLaunchKernelGGL((fused_step_any<OPT>), dim3(grid), dim3(kBlockThreads), 0, stream,
-                           PHUB_LAUNCH_ARGS);
-        return hipGetLastError();
-    } else {
-        return launch_fused_step_many(p, OPT, grid, stream);
-    }
+    if constexpr (!PULL)
+        if (any_kernel(p.num_workers) == kAnyStream)
+            return launch_fused_step_many(p, OPT, grid, stream);
+    hipLaunchKernelGGL((fused_step_any<OPT, PULL>), dim3(grid), dim3(kBlockThreads), 0, stream,
+                       PHUB_LAUNCH_ARGS);
+    return hipGetLastError();
 }
 
+// (A load window that takes more than three phases, in a build that sets its
+// depth, has no fixed-N kernel.)
 template <int NW, int OPT, bool PULL>
 hipError_t launch_one(const StepParams& p, int grid, hipStream_t stream) {
     constexpr int S = kStates<OPT>;
@@ -499,7 +509,7 @@ bool takes_tile_pool(int num_workers, int optimizer) {
 hipError_t launch_fused_step(const StepParams& p, int optimizer, int grid, hipStream_t stream) {
     if (p.pool_count > 0 && (p.merge || !takes_tile_pool(p.num_workers, optimizer)))
         return hipErrorInvalidValue;  // only the fixed-N fused kernels walk a pool
-    if (!p.merge && !p.heads) return hipErrorInvalidValue;  // the fixed-N kernels read them
+    if (!p.merge && !p.heads) return hipErrorInvalidValue;  // the fused kernels read them
     const bool pull = p.outs && !p.merge;
     switch (optimizer) {
         case kOptMomentum:

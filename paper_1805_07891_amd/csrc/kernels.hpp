@@ -52,7 +52,7 @@ struct DevRem {
 };
 static_assert(sizeof(DevRem) == 32, "DevRem layout");
 
-// The start of one wave's work in a launch of the fixed-N kernels (128
+// The start of one wave's work in a launch of the fused kernels (128
 // bytes), read with one burst of scalar loads at the start of the launch:
 // the wave's four bins (as offsets into the tile and remainder tables) and
 // the first descriptor of each (zeros where the bin is empty).  Without it
@@ -211,7 +211,7 @@ struct StepParams {
     const int32_t* tile_begin;    // 2 * bins + 1 offsets into tiles
     const DevRem* rems;           // grouped by bin
     const int32_t* rem_begin;     // 2 * bins + 1 offsets into rems
-    const WaveHead* heads;        // one per wave (the fixed-N kernels read these, not the offsets)
+    const WaveHead* heads;        // one per wave (the fused kernels read these, not the offsets)
     int64_t streamed_tiles;       // full tiles of all streamed bins
     const float* const* grads;    // [row * num_workers + worker], 16-byte aligned
     float* const* outs;           // same layout: model buffers that receive w' (pushpull), or null
@@ -314,8 +314,18 @@ constexpr int stream_block(int num_workers, int num_states) {
     return num_workers > kMaxFixedWorkers ? 6 : kStreamBlock[num_states - 1][num_workers - 1];
 }
 
-// The fused pass of launch_fused_step for worker counts without a fixed-N
-// kernel (no model buffers, no merge buffer, no pool).
+// The kernel of a step (no model buffers) without a fixed-N kernel: batches
+// of workers' loads issued and drained (fused_step_any), or the stream walk
+// (fused_step_many), whose pieces take at least two blocks of loads.
+enum AnyKernel { kAnyBatches, kAnyStream };
+constexpr int kManyBlock = 6;  // loads of a block
+
+constexpr AnyKernel any_kernel(int num_workers) {
+    return num_workers <= kManyBlock ? kAnyBatches : kAnyStream;
+}
+
+// The fused pass of launch_fused_step with fused_step_many: more than
+// kManyBlock workers (no model buffers, no merge buffer, no pool).
 hipError_t launch_fused_step_many(const StepParams& p, int optimizer, int grid,
                                   hipStream_t stream);
 

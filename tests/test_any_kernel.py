@@ -1,0 +1,31 @@
+"""Which kernel runs a step without a fixed-N kernel (CPU): the choice on the
+host, natively, and that builds whose load window leaves a worker count
+without a fixed-N kernel still hold one that takes it."""
+
+import os
+import re
+import subprocess
+
+from paper_1805_07891_amd import build
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+def test_choice_on_the_host(tmp_path):
+    exe = tmp_path / "check"
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                           f"-I{build.CSRC}", os.path.join(HERE, "native", "any_kernel_check.cpp"),
+                           "-o", str(exe)])
+    out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
+    assert out.returncode == 0, out.stderr
+
+
+def test_a_window_without_fixed_kernels_keeps_one_for_few_workers(tmp_path):
+    """A ring of 7 loads takes seven phases for most worker counts (plain SGD
+    here): those run the batched any-N kernel, which takes every count."""
+    asm = open(build.device_assembly(str(tmp_path / "ring7.s"),
+                                     defines=["PHUB_LOADS_AHEAD=6", "PHUB_STEP_PART=4"])).read()
+    names = re.findall(r"^\s+\.name:\s+(\S+)", asm, re.M)
+    fixed = {int(m.group(1)) for m in (re.search(r"fused_step_fixedILi(\d+)ELi2ELb0E", n) for n in names) if m}
+    assert {n for n in range(1, 17) if 4 * (n + 1) % 7 == 0} <= fixed and not fixed & {1, 2, 3, 4, 5}
+    assert any("fused_step_anyILi2ELb0E" in n for n in names)
