@@ -353,7 +353,7 @@ __global__ __launch_bounds__(kBlockThreads) void optimize_only(PHUB_KERNEL_ARGS,
 template <int OPT, bool PULL>
 hipError_t launch_any(const StepParams& p, int grid, hipStream_t stream) {
     if constexpr (!PULL)
-        if (any_kernel(p.num_workers) == kAnyStream)
+        if (any_kernel(p.num_workers, p.load) == kAnyStream)
             return launch_fused_step_many(p, OPT, grid, stream);
     hipLaunchKernelGGL((fused_step_any<OPT, PULL>), dim3(grid), dim3(kBlockThreads), 0, stream,
                        PHUB_LAUNCH_ARGS);
@@ -382,7 +382,7 @@ hipError_t launch_pull(const StepParams& p, int grid, hipStream_t stream) {
     if constexpr (!PULL)  // (the streamed walk takes no tile pool)
         if (p.pool_count == 0 && has_fixed_kernel(p.num_workers) &&
             stream_block(p.num_workers, kStates<OPT>) &&
-            p.streamed_tiles >=
+            p.load.streamed >=
                 int64_t(kStreamMinTiles[kStates<OPT> - 1]) * grid * kWavesPerBlock)
             return launch_stream<OPT>(p, grid, stream);
     switch (p.num_workers) {

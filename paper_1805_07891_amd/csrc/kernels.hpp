@@ -199,6 +199,14 @@ struct OptArgs {
     uint32_t wb_window;
 };
 
+// How a launch's full tiles lie on its waves.
+struct TileLoad {
+    int64_t streamed;  // full tiles of all streamed bins
+    int64_t resident;  // full tiles of all cache-resident bins
+    int64_t busiest;   // the most one wave has, of both
+    int64_t waves;     // one per SIMD of the whole device, launched or not
+};
+
 // The schedule of one launch has two bins per wave.  With
 // bins = grid * kBlockThreads / 64 waves, the bin tables hold 2 * bins + 1
 // offsets: wave w's cache-resident bin is [begin[w], begin[w+1]) (its state
@@ -212,7 +220,7 @@ struct StepParams {
     const DevRem* rems;           // grouped by bin
     const int32_t* rem_begin;     // 2 * bins + 1 offsets into rems
     const WaveHead* heads;        // one per wave (the fused kernels read these, not the offsets)
-    int64_t streamed_tiles;       // full tiles of all streamed bins
+    TileLoad load;
     const float* const* grads;    // [row * num_workers + worker], 16-byte aligned
     float* const* outs;           // same layout: model buffers that receive w' (pushpull), or null
     float* merge;                 // unfused ablation: sum buffer laid out like W, or null (fused)
@@ -262,6 +270,10 @@ struct DeviceTables {
 int64_t append_device_tables(const Plan& plan, const std::vector<VirtualKey>& vkeys,
                              const std::vector<int64_t>& row_arena_offset, int bins,
                              DeviceTables* out);
+
+// How the tiles of the launch whose block of 2 * bins + 1 offsets starts at
+// `block` in dt.tile_begin lie on its waves.
+TileLoad tile_load(const DeviceTables& dt, size_t block, int bins, int64_t waves);
 
 // Sets the calling thread's error message (phub_last_error) and returns code.
 int report_error(int code, const std::string& message);
@@ -320,8 +332,21 @@ constexpr int stream_block(int num_workers, int num_states) {
 enum AnyKernel { kAnyBatches, kAnyStream };
 constexpr int kManyBlock = 6;  // loads of a block
 
-constexpr AnyKernel any_kernel(int num_workers) {
-    return num_workers <= kManyBlock ? kAnyBatches : kAnyStream;
+// The stream walk keeps six loads in flight per wave, a batch thirty-two: the
+// stream is the faster where the chip's waves share the work, the batches
+// where a few of them have most of it (chunks kept whole, a grid of few
+// workgroups), and each waits for memory's latency.  The share of the chip
+// that is busy until the busiest wave ends, batches -> stream (17 to 64
+// workers, the three optimizers): 1/8 0.75-0.86 of the speed, 1/4 0.81-0.90,
+// 1/2 0.92-1.0, 5/8 0.92-1.04, 3/4 1.01-1.10, 7/8 1.07-1.14.  Up to two tiles
+// a wave the schedules that phub_init deals are never uneven in that sense.
+constexpr bool few_waves_busy(const TileLoad& l) {
+    return l.busiest > 2 && 8 * (l.streamed + l.resident) <= 5 * l.busiest * l.waves;
+}
+
+constexpr AnyKernel any_kernel(int num_workers, const TileLoad& load) {
+    if (num_workers <= kManyBlock || few_waves_busy(load)) return kAnyBatches;
+    return kAnyStream;
 }
 
 // The fused pass of launch_fused_step with fused_step_many: more than

@@ -145,7 +145,7 @@ struct phub_job {
     phub::DevRem* d_rems = nullptr;
     int32_t* d_rem_begin = nullptr;   // same layout
     phub::WaveHead* d_heads = nullptr;  // num_rgroups blocks of bins heads
-    std::vector<int64_t> streamed_tiles;  // per readiness group
+    std::vector<phub::TileLoad> loads;  // per readiness group
     std::vector<int32_t> pool_begin;  // per readiness group: its tile pool in d_tiles
     std::vector<int32_t> pool_count;  // (0: the group's schedule is static)
     unsigned long long* d_counters = nullptr;  // takes from the pools: per group, never reset
@@ -383,7 +383,7 @@ int launch_group(phub_job* j, int g) {
         p.rems = j->d_rems;
         p.rem_begin = j->d_rem_begin + size_t(g) * (2 * size_t(j->bins) + 1);
         p.heads = j->d_heads + size_t(g) * size_t(j->bins);
-        p.streamed_tiles = j->streamed_tiles[g];
+        p.load = j->loads[g];
         p.grads = j->d_grads;
         p.outs = pull ? j->d_outs : nullptr;
         p.merge = j->merge;
@@ -493,6 +493,14 @@ int64_t append_device_tables(const Plan& plan, const std::vector<VirtualKey>& vk
         out->rem_begin.push_back(int32_t(out->rems.size()));
     }
     return elems;
+}
+
+TileLoad tile_load(const DeviceTables& dt, size_t block, int bins, int64_t waves) {
+    const int32_t* tb = dt.tile_begin.data() + block;
+    TileLoad l{tb[2 * bins] - tb[bins], tb[bins] - tb[0], 0, waves};
+    for (int w = 0; w < bins; ++w)
+        l.busiest = std::max<int64_t>(l.busiest, tb[w + 1] - tb[w] + tb[bins + w + 1] - tb[bins + w]);
+    return l;
 }
 
 void append_wave_heads(const DeviceTables& dt, size_t block, int bins,
@@ -907,7 +915,10 @@ int phub_init_ex(phub_job** out, int num_workers, int num_keys, const int64_t* k
                         goto fail_cleanup;
                     }
                     if (ph == 0) j->resident_bytes += elems * elem_state_bytes;
-                    if (ph == 1) j->streamed_tiles.push_back(int64_t(dt.tiles.size() - t0));
+                    if (ph == 1)
+                        j->loads.push_back(phub::tile_load(
+                            dt, size_t(g) * (2 * size_t(j->bins) + 1), j->bins,
+                            int64_t(cus) * (phub::kBlockThreads / 64)));
                     if (ph == 1 && j->dynamic) {
                         // the streamed full tiles become the group's pool, in
                         // address order; its bins keep their remainders only

@@ -1,15 +1,52 @@
 // The choice of the any-N kernel on the host.  Exit status 0 when all hold.
 #include <cstdio>
+#include <cstdlib>
+#include <vector>
 
 #include "kernels.hpp"
 
+using namespace phub;
+
+static void check(bool ok, const char* what, int64_t a = 0, int64_t b = 0) {
+    if (ok) return;
+    std::fprintf(stderr, "%s (%lld, %lld)\n", what, (long long)a, (long long)b);
+    std::exit(1);
+}
+
+// The load of `keys` dealt over `bins` of a device of `waves` waves.
+static TileLoad dealt(const std::vector<int64_t>& keys, int bins, int64_t waves) {
+    Plan p;
+    if (!build_dealt(int(keys.size()), keys.data(), kTileElems, 100, bins, &p, false).empty()) std::exit(2);
+    TileLoad l{0, 0, 0, waves};
+    for (int b = 0; b < bins; ++b) {
+        int64_t tiles = 0;
+        for (int64_t i = p.bin_begin[b]; i < p.bin_begin[b + 1]; ++i)
+            tiles += p.segments[i].count / kTileElems;
+        l.streamed += tiles;
+        l.busiest = tiles > l.busiest ? tiles : l.busiest;
+    }
+    return l;
+}
+
 int main() {
-    using namespace phub;
+    const int64_t waves = 1024;
     // a piece of the stream walk takes at least two blocks: never below
     for (int n = 1; n <= kMaxWorkers; ++n)
-        if ((any_kernel(n) == kAnyBatches) != (n <= kManyBlock)) {
-            std::fprintf(stderr, "%d workers\n", n);
-            return 1;
-        }
+        check((any_kernel(n, {50 * waves, 0, 50, waves}) == kAnyBatches) == (n <= kManyBlock), "workers", n);
+    // jobs of the default schedule on the default grid share the chip's waves
+    for (int64_t elems : {1, 1000, 500000, 1048576, 1050000, 1300000, 2097152, 2100000, 3145728,
+                          3200000, 5000000, 25557032})
+        check(any_kernel(17, dealt({elems, 77, 3001}, int(waves), waves)) == kAnyStream, "dealt", elems);
+    // chunks of 8 tiles kept whole: items each on a wave of its own, or two
+    for (int64_t items : {1, 3, 128, 512, 640})
+        check(any_kernel(33, {8 * items, 0, 8, waves}) == kAnyBatches, "few whole chunks", items);
+    for (int64_t items : {768, 1024, 1536, 5000})
+        check(any_kernel(33, {8 * items, 0, 8 * ((items + waves - 1) / waves), waves}) == kAnyStream,
+              "whole chunks", items);
+    // a grid of few workgroups
+    for (int grid : {1, 32, 64, 128, 160})
+        check(any_kernel(64, dealt({4000000}, 4 * grid, waves)) == kAnyBatches, "small grid", grid);
+    for (int grid : {192, 224, 256, 512})
+        check(any_kernel(64, dealt({4000000}, 4 * grid, waves)) == kAnyStream, "grid", grid);
     return 0;
 }

@@ -14,8 +14,9 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 def test_choice_on_the_host(tmp_path):
     exe = tmp_path / "check"
     subprocess.check_call(["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
-                           f"-I{build.CSRC}", os.path.join(HERE, "native", "any_kernel_check.cpp"),
-                           "-o", str(exe)])
+                           f"-I{build.CSRC}",
+                           os.path.join(HERE, "native", "any_kernel_check.cpp"),
+                           os.path.join(build.CSRC, "plan.cpp"), "-o", str(exe)])
     out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
     assert out.returncode == 0, out.stderr
 
