@@ -28,8 +28,9 @@ GRADIENTS_CACHED_LIB = os.path.join(PKG, "libphub_gradients_cached.so")
 PROBE_SOURCES = ["probe.hip"]
 
 SOURCES = ["plan.cpp", "phub_api.cpp", "fused_step.hip", "fused_stream.hip", "fused_many.hip",
-           "put_pointers.hip", "step_noalloc.hip"]
-HEADERS = ["plan.hpp", "kernels.hpp", "device.hpp", "tile_walk.hpp", "stream_walk.hpp"]
+           "fused_many_shared.hip", "put_pointers.hip", "step_noalloc.hip"]
+HEADERS = ["plan.hpp", "kernels.hpp", "device.hpp", "tile_walk.hpp", "stream_walk.hpp",
+           "many_walk.hpp"]
 # Sources that hold many kernels, and the parts (PHUB_STEP_PART) that they are
 # compiled in
 PARTS = {"fused_step.hip": range(8), "fused_stream.hip": range(0, 8, 2)}

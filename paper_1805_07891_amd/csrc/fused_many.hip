@@ -29,109 +29,19 @@
 // 8 up to 2).
 #include <hip/hip_runtime.h>
 
-#include <cstdint>
-
-#include "device.hpp"
 #include "kernels.hpp"
-#include "stream_walk.hpp"
+#include "many_walk.hpp"
 
 namespace phub {
 
-namespace {
-
-// Loads of a block, and in flight.
-constexpr int B = kManyBlock;
-static_assert(kMaxFixedWorkers >= B, "every piece takes at least two blocks");
-
-// The last 1-3 elements of each remainder of a bin.  Lane 4 k + e of a load
-// takes element e of worker 16 i + k, so that 64 workers' loads go out
-// together; the sum then folds them in worker order.
-template <int OPT>
-__device__ __forceinline__ void walk_ragged(const DevRem* __restrict__ rems, int32_t rb, int32_t re,
-                                            const float* const* __restrict__ grads, int n,
-                                            float* const* state, OptArgs o) {
-    constexpr int S = kStates<OPT>;
-    constexpr int G = 4;
-    const int lane = int(threadIdx.x & 63u);
-    const int e = lane & 3;
-    for (int32_t r = rb; r < re; ++r) {
-        const DevRem d = rems[r];
-        const int ragged = d.count & 3;
-        if (!ragged) continue;
-        const int64_t done = d.count & ~3;
-        const PHUB_GLOBAL uint64_t* row =
-            (const PHUB_GLOBAL uint64_t*)grads + int64_t(d.key) * n;
-        const bool mine = lane < ragged;
-        float st[S];
-        if (mine) {
-#pragma unroll
-            for (int i = 0; i < S; ++i) st[i] = load1(state[i], d.arena_offset + done + lane);
-        }
-        float s = -0.0f;
-        for (int w0 = 0; w0 < n; w0 += 16 * G) {
-            float x[G];
-#pragma unroll
-            for (int i = 0; i < G; ++i) {
-                const int w = w0 + 16 * i + (lane >> 2);
-                x[i] = 0.0f;
-                if (w < n && e < ragged)
-                    x[i] = load1(reinterpret_cast<const float*>(row[w]), d.offset + done + e);
-            }
-#pragma unroll
-            for (int i = 0; i < G; ++i)
-                for (int k = 0; k < 16; ++k)
-                    if (w0 + 16 * i + k < n) s = s + __shfl(x[i], 4 * k + e);
-        }
-        if (mine) {
-            update<OPT>(s, st, o);
-#pragma unroll
-            for (int i = 0; i < S; ++i) store1(state[i], d.arena_offset + done + lane, st[i]);
-        }
-    }
-}
-
-template <int OPT>
-__global__ __launch_bounds__(kBlockThreads)
-    __attribute__((amdgpu_waves_per_eu(1, 1))) void fused_step_many(PHUB_KERNEL_ARGS) {
-    float* const state[3] = {weights, moments, second};
-    const uint32_t wave = wave_index();
-    constexpr int S = kStates<OPT>;
-    __shared__ f4 stash_lds[kWavesPerBlock * kStashPieces<S> * S * 64];
-    PHUB_LDS f4* stash = (PHUB_LDS f4*)stash_lds +
-                         (threadIdx.x >> 6) * (kStashPieces<S> * S * 64) + (threadIdx.x & 63u);
-    const WaveHead h = heads[wave];
-    walk_units<B, OPT, false>(tiles, h.tiles_streamed[0], h.tiles_streamed[1], grads, num_workers,
-                           state, o, stash);
-    walk_units<B, OPT, true>(tiles, h.tiles_resident[0], h.tiles_resident[1], grads, num_workers,
-                             state, o, stash);
-    walk_units<B, OPT, true>(rems, h.rems_resident[0], h.rems_resident[1], grads, num_workers,
-                             state, o, stash);
-    walk_units<B, OPT, false>(rems, h.rems_streamed[0], h.rems_streamed[1], grads, num_workers,
-                              state, o, stash);
-    walk_ragged<OPT>(rems, h.rems_streamed[0], h.rems_streamed[1], grads, num_workers, state, o);
-    walk_ragged<OPT>(rems, h.rems_resident[0], h.rems_resident[1], grads, num_workers, state, o);
-}
-
-template <int OPT>
-hipError_t launch(const StepParams& p, int grid, hipStream_t stream) {
-    hipLaunchKernelGGL((fused_step_many<OPT>), dim3(grid), dim3(kBlockThreads), 0, stream,
-                       p.tiles, p.tile_begin, p.rems, p.rem_begin, p.heads, p.grads, p.outs,
-                       p.weights, p.moments, p.second, p.opt, p.num_workers, p.pool, p.pool_count,
-                       p.pool_counters, p.pool_launch);
-    return hipGetLastError();
-}
-
-}  // namespace
-
 hipError_t launch_fused_step_many(const StepParams& p, int optimizer, int grid,
                                   hipStream_t stream) {
-    // (a piece takes at least two blocks: the window's pointers run one ahead)
-    if (p.num_workers <= B || p.outs || p.merge || p.pool_count > 0) return hipErrorInvalidValue;
+    if (!many_takes(p)) return hipErrorInvalidValue;
     switch (optimizer) {
-        case kOptMomentum: return launch<kOptMomentum>(p, grid, stream);
-        case kOptNesterov: return launch<kOptNesterov>(p, grid, stream);
-        case kOptSgd: return launch<kOptSgd>(p, grid, stream);
-        case kOptAdam: return launch<kOptAdam>(p, grid, stream);
+        case kOptMomentum: return launch_many<stash_tiles(2), kOptMomentum>(p, grid, stream);
+        case kOptNesterov: return launch_many<stash_tiles(2), kOptNesterov>(p, grid, stream);
+        case kOptSgd: return launch_many<stash_tiles(1), kOptSgd>(p, grid, stream);
+        case kOptAdam: return launch_many<stash_tiles(3), kOptAdam>(p, grid, stream);
         default: return hipErrorInvalidValue;
     }
 }

@@ -352,9 +352,11 @@ __global__ __launch_bounds__(kBlockThreads) void optimize_only(PHUB_KERNEL_ARGS,
 
 template <int OPT, bool PULL>
 hipError_t launch_any(const StepParams& p, int grid, hipStream_t stream) {
-    if constexpr (!PULL)
-        if (any_kernel(p.num_workers, p.load) == kAnyStream)
-            return launch_fused_step_many(p, OPT, grid, stream);
+    if constexpr (!PULL) {
+        const AnyKernel k = any_kernel(p.num_workers, p.load);
+        if (k == kAnyStream) return launch_fused_step_many(p, OPT, grid, stream);
+        if (k == kAnyStreamShared) return launch_fused_step_many_shared(p, OPT, grid, stream);
+    }
     hipLaunchKernelGGL((fused_step_any<OPT, PULL>), dim3(grid), dim3(kBlockThreads), 0, stream,
                        PHUB_LAUNCH_ARGS);
     return hipGetLastError();

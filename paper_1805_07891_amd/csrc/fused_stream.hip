@@ -32,12 +32,13 @@ __global__ __launch_bounds__(kBlockThreads)
     float* const state[3] = {weights, moments, second};
     const uint32_t wave = wave_index();
     constexpr int S = kStates<OPT>;
-    __shared__ f4 stash_lds[kWavesPerBlock * kStashPieces<S> * S * 64];
-    PHUB_LDS f4* stash = (PHUB_LDS f4*)stash_lds +
-                         (threadIdx.x >> 6) * (kStashPieces<S> * S * 64) + (threadIdx.x & 63u);
+    constexpr int P = stash_tiles(S) * kVecPerLane;  // pieces of the stash
+    __shared__ f4 stash_lds[kWavesPerBlock * P * S * 64];
+    PHUB_LDS f4* stash = (PHUB_LDS f4*)stash_lds + (threadIdx.x >> 6) * (P * S * 64) +
+                         (threadIdx.x & 63u);
     const WaveHead h = heads[wave];
-    walk_units<B, OPT, false>(tiles, h.tiles_streamed[0], h.tiles_streamed[1], grads, num_workers,
-                              state, o, stash);
+    walk_units<B, OPT, false, P>(tiles, h.tiles_streamed[0], h.tiles_streamed[1], grads,
+                                 num_workers, state, o, stash);
     walk_tiles<NW, OPT, true, false>(tiles, h.tiles_resident[0], h.tiles_resident[1],
                                      h.first_resident, grads, outs, state, o, nullptr);
     walk_rems<NW, OPT, true, false>(rems, h.rems_resident[0], h.rems_resident[1],

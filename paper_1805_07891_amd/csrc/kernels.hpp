@@ -329,7 +329,7 @@ constexpr int stream_block(int num_workers, int num_states) {
 // The kernel of a step (no model buffers) without a fixed-N kernel: batches
 // of workers' loads issued and drained (fused_step_any), or the stream walk
 // (fused_step_many), whose pieces take at least two blocks of loads.
-enum AnyKernel { kAnyBatches, kAnyStream };
+enum AnyKernel { kAnyBatches, kAnyStream, kAnyStreamShared };
 constexpr int kManyBlock = 6;  // loads of a block
 
 // The stream walk keeps six loads in flight per wave, a batch thirty-two: the
@@ -344,15 +344,34 @@ constexpr bool few_waves_busy(const TileLoad& l) {
     return l.busiest > 2 && 8 * (l.streamed + l.resident) <= 5 * l.busiest * l.waves;
 }
 
+// State that is cached needs no bursts.  Up to three tiles a wave the stream
+// is still the faster, by what a launch's ends weigh there; its stash, small
+// enough that tenants share a compute unit (fused_many_shared.hip), is for
+// the loads not to wait for stores.  With more tiles the batches are level or
+// faster.  Batches -> stream, the speed of one job and of four at once (17 to
+// 64 workers, the three optimizers): 1 tile 1.32-1.44 and 0.99-1.15, 2 tiles
+// 1.11-1.22 and 0.95-1.02, 3 tiles 0.99-1.16 and 0.98-1.07, 4 tiles
+// 0.96-1.09 and 0.98-1.05, 25.6 M parameters with 21 0.97 (one job).
+constexpr int64_t kSharedTiles = 3;
+constexpr int kSharedStashBytesPerWave = 16 * 1024;
+constexpr int shared_stash_tiles(int num_states) {
+    return kSharedStashBytesPerWave / (num_states * 4 * 1024);
+}
+
 constexpr AnyKernel any_kernel(int num_workers, const TileLoad& load) {
     if (num_workers <= kManyBlock || few_waves_busy(load)) return kAnyBatches;
+    if (load.resident >= load.streamed)  // (none of either: remainders only)
+        return load.busiest <= kSharedTiles ? kAnyStreamShared : kAnyBatches;
     return kAnyStream;
 }
 
-// The fused pass of launch_fused_step with fused_step_many: more than
-// kManyBlock workers (no model buffers, no merge buffer, no pool).
+// The fused pass of launch_fused_step with fused_step_many, its whole stash or
+// the shared one: more than kManyBlock workers (no model buffers, no merge
+// buffer, no pool).
 hipError_t launch_fused_step_many(const StepParams& p, int optimizer, int grid,
                                   hipStream_t stream);
+hipError_t launch_fused_step_many_shared(const StepParams& p, int optimizer, int grid,
+                                         hipStream_t stream);
 
 // The same for worker counts with a fixed-N kernel where stream_block is not
 // 0 (OPT an OptKind).

@@ -90,14 +90,10 @@ __device__ __forceinline__ const float* lane_base(uint64_t p, int j) {
 }
 
 // Burst write-back of the streamed tiles' state, as in fused_step.hip: a
-// finished piece's state goes to a stash in LDS (kStashPieces pieces per
-// wave, lane l holding entry l of every 64), and the wave writes the stash
+// finished piece's state goes to a stash in LDS (P pieces per wave, lane l holding entry l of every 64), and the wave writes the stash
 // back in one run of stores when the chip-wide write window is open (looked
 // at after every block of loads), when the stash is full, or after its last
 // piece.  Each lane reads back only what it wrote: no barrier.
-template <int S>
-constexpr int kStashPieces = stash_tiles(S) * kVecPerLane;
-
 template <int S>
 struct Stash {
     PHUB_LDS f4* lds;  // the lane's entry of the wave's first piece
@@ -139,12 +135,13 @@ struct Stash {
     uint32_t lane = threadIdx.x & 63u;
 };
 
-template <int B, int OPT, bool RES, typename DESC>
+template <int B, int OPT, bool RES, int P, typename DESC>
 __device__ __forceinline__ void walk_units(const DESC* desc, int32_t begin, int32_t end,
                                            const float* const* grads, int n, float* const* state,
                                            OptArgs o, PHUB_LDS f4* stash_lds) {
     constexpr int S = kStates<OPT>;
     constexpr bool STASH = sizeof(DESC) == sizeof(DevTile);
+    static_assert(P >= 1 && P <= 64 && P % kVecPerLane == 0, "a lane holds one piece's place");
     Stash<S> stash{stash_lds};
     UnitList<DESC> list(desc, begin, end);
     if (!list.more()) return;
@@ -181,7 +178,7 @@ __device__ __forceinline__ void walk_units(const DESC* desc, int32_t begin, int3
         // the bases of the block being issued; q: of the one after it.
         for (int w0 = 0; w0 < last; w0 += B) {
             if constexpr (STASH) {
-                if (stash.count && (stash.count == kStashPieces<S> ||
+                if (stash.count && (stash.count == P ||
                                     in_write_window(o.wb_period, o.wb_window)))
                     stash.template write_back<RES>(state);
             }

@@ -1,6 +1,7 @@
 // The choice of the any-N kernel on the host.  Exit status 0 when all hold.
 #include <cstdio>
 #include <cstdlib>
+#include <utility>
 #include <vector>
 
 #include "kernels.hpp"
@@ -35,8 +36,22 @@ int main() {
         check((any_kernel(n, {50 * waves, 0, 50, waves}) == kAnyBatches) == (n <= kManyBlock), "workers", n);
     // jobs of the default schedule on the default grid share the chip's waves
     for (int64_t elems : {1, 1000, 500000, 1048576, 1050000, 1300000, 2097152, 2100000, 3145728,
-                          3200000, 5000000, 25557032})
-        check(any_kernel(17, dealt({elems, 77, 3001}, int(waves), waves)) == kAnyStream, "dealt", elems);
+                          3200000, 5000000, 25557032}) {
+        TileLoad l = dealt({elems, 77, 301}, int(waves), waves);
+        check(any_kernel(17, l) == (l.streamed ? kAnyStream : kAnyStreamShared), "dealt", elems);
+        // the same with its state cached, whole and by halves
+        std::swap(l.streamed, l.resident);
+        check(any_kernel(17, l) == (l.busiest <= kSharedTiles ? kAnyStreamShared : kAnyBatches), "cached",
+              elems);
+        l.streamed = l.resident;
+        check(any_kernel(17, l) == (l.busiest <= kSharedTiles ? kAnyStreamShared : kAnyBatches), "half",
+              elems);
+        l.streamed = l.resident + 1;
+        check(any_kernel(17, l) == kAnyStream, "mostly streamed", elems);
+    }
+    for (int s : {1, 2, 3})  // two launches' workgroups fit a compute unit
+        check(shared_stash_tiles(s) >= 1 &&
+                  2 * 4 * shared_stash_tiles(s) * s * 4096 <= 160 * 1024, "shared stash", s);
     // chunks of 8 tiles kept whole: items each on a wave of its own, or two
     for (int64_t items : {1, 3, 128, 512, 640})
         check(any_kernel(33, {8 * items, 0, 8, waves}) == kAnyBatches, "few whole chunks", items);

@@ -21,6 +21,23 @@ def test_choice_on_the_host(tmp_path):
     assert out.returncode == 0, out.stderr
 
 
+def test_the_shared_stash_leaves_room_for_a_second_launch(tmp_path):
+    asm = open(build.device_assembly(str(tmp_path / "shared.s"), "fused_many_shared.hip")).read()
+    blocks = asm.split("  - .agpr_count:")[1:]
+    assert len(blocks) == 4
+    for block in blocks:
+        tiles, opt = map(int, re.search(r"fused_step_manyILi(\d+)ELi(\d)E", block).groups())
+
+        def field(key):
+            return int(re.search(rf"\.{key}:\s+(\d+)", block).group(1))
+
+        states = {0: 2, 1: 2, 2: 1, 3: 3}[opt]
+        assert tiles == 4 // states
+        assert field("group_segment_fixed_size") == 4 * tiles * states * 4096 <= 80 * 1024
+        assert field("vgpr_count") <= 128  # more than one wave per SIMD
+        assert field("private_segment_fixed_size") == 0 and field("vgpr_spill_count") == 0
+
+
 def test_a_window_without_fixed_kernels_keeps_one_for_few_workers(tmp_path):
     """A ring of 7 loads takes seven phases for most worker counts (plain SGD
     here): those run the batched any-N kernel, which takes every count."""

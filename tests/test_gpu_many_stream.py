@@ -1,9 +1,10 @@
-"""GPU parity of the any-N stream walk where it runs: the device's whole grid
-with three and more full tiles a wave, every filling of its last block of
+"""GPU parity of the any-N kernels on the device's whole grid with two and more
+full tiles a wave: the stream walk at every filling of its last block of
 loads, every optimizer, state streamed and partly cached, and a key beyond
 the 2^20 float4 that are folded into the gradients' bases (a wave walks tiles
-on both sides of the fold, then another key's); bit-exact against the CPU
-oracle."""
+on both sides of the fold, then another key's); cached state up to three
+tiles a wave (the shared stash) and beyond (batches); bit-exact against the
+CPU oracle."""
 
 import numpy as np
 import pytest
@@ -15,6 +16,7 @@ from paper_1805_07891_amd.workloads import Job, key_offsets
 pytestmark = pytest.mark.gpu
 
 KEYS = (5, 1024 * 1024 * 2 + 3, 0, 700001, 1024 * 500, 4097, 1)
+MID = (1024 * 1024 * 2 + 3, 300001, 0, 5)
 FOLD = (4300003, 1300001, 5, 0, 1023)
 
 
@@ -22,7 +24,9 @@ FOLD = (4300003, 1300001, 5, 0, 1023)
     (17, "nesterov", FOLD, 0), (17, "adam", FOLD, 0), (23, "sgd", FOLD, 0), (18, "momentum", KEYS, 0),
     (19, "nesterov", KEYS, 0), (21, "nesterov", KEYS, None), (22, "sgd", KEYS, None),
     (25, "adam", KEYS, 0), (17, "momentum", FOLD, 8 * 1000000), (33, "adam", KEYS, 12 * 1000000),
-    (40, "nesterov", KEYS, None), (65, "momentum", KEYS, None)])
+    (40, "nesterov", KEYS, None), (65, "momentum", KEYS, None),
+    (17, "momentum", MID, 1 << 28), (22, "sgd", MID, 1 << 28), (33, "adam", MID, 1 << 28),
+    (19, "nesterov", KEYS, 1 << 28), (25, "adam", KEYS, 1 << 28), (17, "sgd", FOLD, 1 << 28)])
 def test_whole_grid(n, opt, keys, resident):
     import torch
     print("stream", n, opt, sum(keys), resident, flush=True)
