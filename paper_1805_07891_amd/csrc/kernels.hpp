@@ -103,18 +103,26 @@ constexpr bool burst_write_back(int num_workers, int num_states) {
            num_workers >= kBurstMinWorkers[num_states - 1];
 }
 
-// Whether the full tiles left over from the last whole round of a dealt
-// schedule (build_dealt) are cut evenly over the waves: only where their
-// state is streamed and written back in bursts.  Measured on MI355X, whole
-// -> cut: 8 workers over 1.2 M parameters 12.2 -> 10.8 us, over 4.7 M 39.3
-// -> 37.4, 16 over 2.4 M 34.7 -> 32.4, pushpull with 8 over 1.2 M 23.0 ->
-// 20.7.  The other kernels run a second tile on in the load window of the
-// first, and a piece costs its own trip to memory: 2 workers over 1.2 M 6.8
-// -> 7.6 us, 4 over 1.2 M 8.3 -> 9.1, Adam with 8 over 1.7 M 19.4 -> 20.4, 17
-// over 1.4 M 23.2 -> 24.4, cached state with 8 over 1.2 M 11.4 -> 12.5; four
-// jobs at once up to 25% (1 worker, Adam, 1.7 M each 37 -> 46).
-constexpr bool cuts_leftover(int num_workers, int num_states, bool streamed, bool unfused) {
-    return streamed && !unfused && burst_write_back(num_workers, num_states);
+// Whole rounds of full tiles from which a dealt schedule (build_dealt) cuts
+// the tiles left over from the last one evenly over the waves; negative:
+// never.  Cut where the state is streamed and written back in bursts.
+// Measured on MI355X, whole -> cut: 8 workers over 1.2 M parameters 12.2 ->
+// 10.8 us, over 4.7 M 39.3 -> 37.4, 16 over 2.4 M 34.7 -> 32.4, pushpull with
+// 8 over 1.2 M 23.0 -> 20.7.  The kernels without bursts run a second tile on
+// in the load window of the first, and a piece costs its own trip to memory:
+// 2 workers over 1.2 M 6.8 -> 7.6 us, 4 over 1.2 M 8.3 -> 9.1, Adam with 8
+// over 1.7 M 19.4 -> 20.4, cached state with 8 over 1.2 M 11.4 -> 12.5; four
+// jobs at once up to 25% (1 worker, Adam, 1.7 M each 37 -> 46).  The any-N
+// stream's piece is a walk of its own (17 workers over 1.4 M 23.2 -> 24.4):
+// below eight rounds 0 to 5% slower, beyond within 1% either way, alone up to
+// 1% faster (64 workers over 25.6 M 1024 -> 1016).  Below one round a cut
+// gives a lone job up to 7%, and costs small jobs that run at the same time
+// about as much (two of 8 workers over 0.6 M 9.3 -> 10.2 us, one 6.7 -> 6.4),
+// since each is then on every compute unit.
+constexpr int cut_rounds(int num_workers, int num_states, bool streamed, bool unfused) {
+    if (!streamed || unfused) return -1;
+    if (!has_fixed_kernel(num_workers)) return 8;
+    return burst_write_back(num_workers, num_states) ? 0 : -1;
 }
 
 // The burst write-back's stash: LDS per wave (the compute unit's 160 KB

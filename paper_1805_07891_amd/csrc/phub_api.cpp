@@ -816,8 +816,8 @@ int phub_init_ex(phub_job** out, int num_workers, int num_keys, const int64_t* k
                             err = phub::build_dealt(int(vk.size()), elems.data(), phub::kTileElems,
                                                     (num_workers + 2 * int64_t(j->num_states)) * 4,
                                                     bins, &plan,
-                                                    phub::cuts_leftover(num_workers, j->num_states,
-                                                                        ph == 1, unfused));
+                                                    phub::cut_rounds(num_workers, j->num_states,
+                                                                     ph == 1, unfused));
                         else
                             err = phub::build_plan(num_workers, int(vk.size()), elems.data(),
                                                    chunk_bytes,

@@ -243,7 +243,7 @@ std::string build_plan(int num_workers, int num_keys, const int64_t* key_elems,
 }
 
 std::string build_dealt(int num_keys, const int64_t* key_elems, int64_t tile_elems,
-                        int64_t bytes_per_elem, int num_bins, Plan* out, bool cut_leftover) {
+                        int64_t bytes_per_elem, int num_bins, Plan* out, int cut_rounds) {
     if (num_bins < 1) return "num_bins must be >= 1, got " + std::to_string(num_bins);
     if (tile_elems < 4 * kPieceAlign || tile_elems % kPieceAlign != 0) return "bad tile size";
     out->segments.clear();
@@ -257,13 +257,10 @@ std::string build_dealt(int num_keys, const int64_t* key_elems, int64_t tile_ele
     }
     // Tiles [0, whole) are dealt in turn; the leftover [whole, tiles) is cut
     // into pieces of `piece` elements, one for each bin that need not take a
-    // remainder, unless a piece would be nearly a tile.  Below one whole round
-    // nothing is cut: two jobs of 8 workers over 0.6 M parameters at once
-    // took 9.3 us with whole tiles and 10.2 with pieces on every wave (one
-    // alone 6.7 and 6.4).
+    // remainder, unless a piece would be nearly a tile.
     int64_t whole = tiles - tiles % num_bins;
     int64_t piece = 0;
-    if (cut_leftover && whole > 0 && whole < tiles && rems < num_bins) {
+    if (cut_rounds >= 0 && tiles / num_bins >= cut_rounds && whole < tiles && rems < num_bins) {
         const int64_t left = (tiles - whole) * tile_elems, bins = num_bins - rems;
         piece = (left + bins - 1) / bins;
         piece = std::max((piece + kPieceAlign - 1) / kPieceAlign * kPieceAlign, 4 * kPieceAlign);

@@ -64,13 +64,13 @@ std::string build_plan(int num_workers, int num_keys, const int64_t* key_elems,
 // tiles of tile_elems elements go to the bins in turn (which is what the
 // longest-processing-time-first rule does with equal items), then the keys'
 // remainders largest first to the least loaded bin; small keys are not
-// bundled (a wave walks its remainders one after another).  cut_leftover:
-// where there is a whole round of tiles and few enough are left over, those
-// are cut into equal pieces so that every bin gets one.  bytes_per_elem:
-// what the step moves per element.
+// bundled (a wave walks its remainders one after another).  Where
+// there are cut_rounds whole rounds of tiles (negative: never) and few enough
+// are left over, those are cut into equal pieces so that every bin gets one.
+// bytes_per_elem: what the step moves per element.
 std::string build_dealt(int num_keys, const int64_t* key_elems, int64_t tile_elems,
                         int64_t bytes_per_elem, int num_bins, Plan* out,
-                        bool cut_leftover = true);
+                        int cut_rounds = 0);
 
 // Full tiles of tile_elems elements and remainders that the LPT schedule's
 // segments would be cut into (the arguments as build_plan's), counted key by

@@ -23,14 +23,15 @@ def test_rule_and_plans(tmp_path):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("n,opt,kw,cut", [
-    (8, None, {}, True), (6, "sgd", {}, True), (14, "adam", {}, True), (32, None, {}, True),
-    (1, "adam", {}, False), (4, None, {}, False), (8, "adam", {}, False), (17, None, {}, False),
-    (8, None, {"resident_bytes": 1 << 28}, False), (8, None, {"unfused": True}, False)])
-def test_segments_of_jobs(n, opt, kw, cut):
+@pytest.mark.parametrize("n,opt,kw,rounds", [
+    (8, None, {}, 0), (6, "sgd", {}, 0), (14, "adam", {}, 0), (32, None, {}, 0),
+    (1, "adam", {}, None), (4, None, {}, None), (8, "adam", {}, None),
+    (17, None, {"resident_bytes": 0}, 8), (21, "adam", {"resident_bytes": 0}, 8),
+    (8, None, {"resident_bytes": 1 << 28}, None), (8, None, {"unfused": True}, None)])
+def test_segments_of_jobs(n, opt, kw, rounds):
     from paper_1805_07891_amd.job import TorchJob
     print("segments", n, opt, kw, flush=True)
-    for tiles, whole_round in ((20, True), (6, False)):  # 8 waves
+    for tiles in (4, 20, 68):  # on 8 waves: none, two and eight whole rounds, four tiles left over
         job = TorchJob(Job("cut", n, (tiles * 1024 + 3,)), "cuda:0", workgroups=2, optimizer=opt, **kw)
-        assert (job.info()[2] > tiles + 1) == (cut and whole_round), tiles
+        assert (job.info()[2] > tiles + 1) == (rounds is not None and tiles // 8 >= rounds), tiles
         job.destroy()
