@@ -132,15 +132,17 @@ typedef struct phub_options {
                                bursts take none of it (they stream as fast as
                                they cache): momentum SGD and plain SGD with
                                6 to 16, 20, 24 or 32 workers, Adam with 14 to
-                               16, 20, 24 or 32, and any other count above 16
-                               whose gradients and state together exceed the
-                               budget's 256 MiB; not unfused.  A job that
-                               will step with pushpull (whose kernels write
-                               the model buffers and have no burst
+                               16, 20, 24 or 32; not unfused.  A job of these
+                               that will step with pushpull (whose kernels
+                               write the model buffers and have no burst
                                write-back) gains from an explicit budget:
                                measured 0.81 against 0.70 of peak for 8
                                workers over 25.6 M parameters with all of its
-                               state cached.  Results do not depend on it. */
+                               state cached.  With any other count above 16,
+                               a job whose gradients and state together
+                               exceed 256 MiB takes its share for its
+                               pushpull steps, and streams all of its state
+                               in the others.  Results do not depend on it. */
     int num_groups;         /* readiness groups (sections 3.2.2-3.2.3: a
                                chunk is aggregated as soon as all of its
                                pieces have arrived).  0: none; the whole step
@@ -360,7 +362,8 @@ int phub_get_stream(phub_job *job, void **hip_stream);
  * number of work segments in the schedule, the bytes of optimizer state
  * (S arrays over the padded arena), and how many of those bytes are
  * scheduled as cache-resident (0: all of the state streams non-temporally;
- * equal to the state bytes, less the padding, when all of it is cached).
+ * equal to the state bytes, less the padding, when all of it is cached),
+ * where only pushpull steps cache (see phub_options.resident_bytes) in those.
  * Any output may be NULL.
  */
 int phub_job_info(phub_job *job, int *workgroups, int *threads_per_group, int64_t *segments,

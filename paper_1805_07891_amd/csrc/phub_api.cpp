@@ -141,11 +141,16 @@ struct phub_job {
     float* second = nullptr;   // Adam's second moment, else null
     float* merge = nullptr;  // unfused ablation only: the sum, laid out like W
     phub::DevTile* d_tiles = nullptr;
-    int32_t* d_tile_begin = nullptr;  // num_rgroups blocks of 2 * bins + 1 entries
+    // One schedule per readiness group; with `two_schedules` these are the
+    // pushpull steps', and as many follow for the other steps, which stream
+    // all of the state.
+    bool two_schedules = false;
+    int num_schedules() const { return num_rgroups * (two_schedules ? 2 : 1); }
+    int32_t* d_tile_begin = nullptr;  // num_schedules() blocks of 2 * bins + 1 entries
     phub::DevRem* d_rems = nullptr;
     int32_t* d_rem_begin = nullptr;   // same layout
-    phub::WaveHead* d_heads = nullptr;  // num_rgroups blocks of bins heads
-    std::vector<phub::TileLoad> loads;  // per readiness group
+    phub::WaveHead* d_heads = nullptr;  // num_schedules() blocks of bins heads
+    std::vector<phub::TileLoad> loads;  // per schedule
     std::vector<int32_t> pool_begin;  // per readiness group: its tile pool in d_tiles
     std::vector<int32_t> pool_count;  // (0: the group's schedule is static)
     unsigned long long* d_counters = nullptr;  // takes from the pools: per group, never reset
@@ -378,12 +383,13 @@ int launch_group(phub_job* j, int g) {
     }
     if (j->rgroup_work[g]) {
         phub::StepParams p{};
+        const size_t s = size_t(g) + (j->two_schedules && !pull ? size_t(j->num_rgroups) : 0);
         p.tiles = j->d_tiles;
-        p.tile_begin = j->d_tile_begin + size_t(g) * (2 * size_t(j->bins) + 1);
+        p.tile_begin = j->d_tile_begin + s * (2 * size_t(j->bins) + 1);
         p.rems = j->d_rems;
-        p.rem_begin = j->d_rem_begin + size_t(g) * (2 * size_t(j->bins) + 1);
-        p.heads = j->d_heads + size_t(g) * size_t(j->bins);
-        p.load = j->loads[g];
+        p.rem_begin = j->d_rem_begin + s * (2 * size_t(j->bins) + 1);
+        p.heads = j->d_heads + s * size_t(j->bins);
+        p.load = j->loads[s];
         p.grads = j->d_grads;
         p.outs = pull ? j->d_outs : nullptr;
         p.merge = j->merge;
@@ -741,24 +747,26 @@ int phub_init_ex(phub_job** out, int num_workers, int num_keys, const int64_t* k
     // parameters with 16 workers 0.82 against 0.79; four concurrent
     // 8-worker jobs 0.77 against 0.76; 25.6 M parameters with 8 workers
     // 0.79 streamed, 0.83 cached while the cache keeps the state from the
-    // previous step and 0.75 after the cache was flushed).  Jobs without
-    // bursts (few workers, the unfused variant) still gain from the cache.
+    // previous step and 0.75 after the cache was flushed).  Steps without
+    // bursts (few workers, the unfused variant, pushpull) still gain from the
+    // cache.
     j->num_states = j->opt == phub::kOptSgd ? 1 : j->opt == phub::kOptAdam ? 3 : 2;
     const int64_t elem_state_bytes = j->num_states * int64_t(sizeof(float));
     {
         std::lock_guard<std::mutex> lk(g_live_mu);
         int64_t budget = resident_bytes;
-        // The any-N kernel bursts too, and measured no slower streamed than
-        // cached at any size, up to 15% faster (25.6 M parameters with 64
-        // workers: 0.844 against 0.73-0.75 of peak): it takes the budget
-        // only where the whole job, gradients included, would fit the cache
-        // (equal there: 0.8 M parameters with 21 workers 13.9 us either way).
+        // The any-N stream bursts too, and a lone job measured no slower
+        // streamed than cached at any size, up to 17% faster (25.6 M
+        // parameters with 64 workers 1018 us against 1192), but its pushpull
+        // steps have no bursts and gain from the cache (25.6 M, 17 workers
+        // 685 us against 755, 33 1359 against 1430, 64 2629 against 2691).  So
+        // by default it takes its share like the jobs without bursts, and
+        // where the whole job, gradients included, would not fit the cache,
+        // only its pushpull steps use it.
         const bool fits = j->arena_elems <= PHUB_DEVICE_CACHE_BYTES / int64_t(sizeof(float)) /
                                                 (num_workers + j->num_states);
-        const bool stream_all =
-            !unfused && (phub::has_fixed_kernel(num_workers)
-                             ? phub::burst_write_back(num_workers, j->num_states)
-                             : !fits);
+        const bool stream_all = !unfused && phub::has_fixed_kernel(num_workers) &&
+                                phub::burst_write_back(num_workers, j->num_states);
         if (budget < 0)
             budget = stream_all ? 0 : std::max<int64_t>(0, PHUB_DEVICE_CACHE_BYTES - g_cache_claimed[j->device]);
         j->resident_elems = std::min(j->arena_elems, budget / elem_state_bytes);
@@ -766,39 +774,43 @@ int phub_init_ex(phub_job** out, int num_workers, int num_keys, const int64_t* k
             j->cache_claim = j->resident_elems * elem_state_bytes;
             g_cache_claimed[j->device] += j->cache_claim;
         }
+        j->two_schedules = resident_bytes < 0 && j->resident_elems > 0 && !unfused &&
+                           !phub::has_fixed_kernel(num_workers) && !fits;
     }
 
-    // Two schedules per readiness group over the group's keys in row order:
+    // Two plans per schedule over its readiness group's keys in row order:
     // phase 0 holds the cache-resident part of the keys, phase 1 the rest.
     // A key that straddles resident_elems is cut at a tile boundary of the
     // key (the part below the cut is resident), so both parts keep the
     // 16-byte alignment of the key's start.  A part is a "virtual key": a
     // row and a first element within the key.
     using VKey = phub::VirtualKey;
-    std::vector<phub::Plan> plans;  // [group * 2 + phase]
+    std::vector<phub::Plan> plans;  // [schedule * 2 + phase]
     std::vector<std::vector<VKey>> vkeys;
     {
         const int groups = workgroups > 0 ? workgroups : cus * PHUB_GROUPS_PER_CU;
         const int bins = groups * (phub::kBlockThreads / 64);
         std::string err;
         try {
-            plans.resize(size_t(j->num_rgroups) * 2);
-            vkeys.resize(size_t(j->num_rgroups) * 2);
-            for (int g = 0; g < j->num_rgroups && err.empty(); ++g) {
+            plans.resize(size_t(j->num_schedules()) * 2);
+            vkeys.resize(size_t(j->num_schedules()) * 2);
+            for (int s = 0; s < j->num_schedules() && err.empty(); ++s) {
+                const int g = s % j->num_rgroups;
+                const int64_t resident_elems = s < j->num_rgroups ? j->resident_elems : 0;
                 for (int r = j->rgroup_row_begin[g]; r < j->rgroup_row_begin[g + 1]; ++r) {
                     const int k = j->key_of_row[r];
                     const int64_t n = key_elems[k], o = j->arena_offset[k];
                     int64_t cut = 0;  // elements of the key that are resident
-                    if (o + n <= j->resident_elems)
+                    if (o + n <= resident_elems)
                         cut = n;
-                    else if (o < j->resident_elems)
-                        cut = (j->resident_elems - o) / phub::kTileElems * phub::kTileElems;
-                    if (cut > 0) vkeys[g * 2].push_back({r, 0, cut});
-                    if (cut < n || n == 0) vkeys[g * 2 + 1].push_back({r, cut, n - cut});
+                    else if (o < resident_elems)
+                        cut = (resident_elems - o) / phub::kTileElems * phub::kTileElems;
+                    if (cut > 0) vkeys[s * 2].push_back({r, 0, cut});
+                    if (cut < n || n == 0) vkeys[s * 2 + 1].push_back({r, cut, n - cut});
                 }
                 for (int ph = 0; ph < 2 && err.empty(); ++ph) {
-                    const std::vector<VKey>& vk = vkeys[g * 2 + ph];
-                    phub::Plan& plan = plans[g * 2 + ph];
+                    const std::vector<VKey>& vk = vkeys[s * 2 + ph];
+                    phub::Plan& plan = plans[s * 2 + ph];
                     if (!vk.empty()) {
                         std::vector<int64_t> elems(vk.size());
                         for (size_t i = 0; i < vk.size(); ++i) elems[i] = vk[i].elems;
@@ -833,7 +845,8 @@ int phub_init_ex(phub_job** out, int num_workers, int num_keys, const int64_t* k
                     while (plan.bin_begin.size() < size_t(bins) + 1)
                         plan.bin_begin.push_back(plan.bin_begin.back());
                     if (!plan.segments.empty()) j->rgroup_work[g] = 1;
-                    j->num_segments += int64_t(plan.segments.size());
+                    if (s + j->num_rgroups >= j->num_schedules())  // the ordinary steps'
+                        j->num_segments += int64_t(plan.segments.size());
                 }
             }
         } catch (const std::bad_alloc&) {
@@ -896,20 +909,20 @@ int phub_init_ex(phub_job** out, int num_workers, int num_keys, const int64_t* k
         // Device form of the schedules: each bin's segments become full tiles
         // (the kernel's straight-line hot loop) and at most one remainder
         // each (partial tile and ragged end), in segment order; one block of
-        // 2 * bins + 1 offsets per readiness group (the resident bins, then
+        // 2 * bins + 1 offsets per schedule (the resident bins, then
         // the streamed ones).  A descriptor's key is the key's row in the
         // pointer table.
         phub::DeviceTables dt;
         {
             std::vector<int64_t> row_arena_offset(num_keys);
             for (int r = 0; r < num_keys; ++r) row_arena_offset[r] = j->arena_offset[j->key_of_row[r]];
-            for (int g = 0; g < j->num_rgroups; ++g) {
+            for (int s = 0; s < j->num_schedules(); ++s) {
                 dt.tile_begin.push_back(int32_t(dt.tiles.size()));
                 dt.rem_begin.push_back(int32_t(dt.rems.size()));
                 for (int ph = 0; ph < 2; ++ph) {
                     const size_t t0 = dt.tiles.size();
                     const int64_t elems = phub::append_device_tables(
-                        plans[g * 2 + ph], vkeys[g * 2 + ph], row_arena_offset, j->bins, &dt);
+                        plans[s * 2 + ph], vkeys[s * 2 + ph], row_arena_offset, j->bins, &dt);
                     if (elems < 0) {
                         rc = fail(PHUB_EINVAL, "schedule too large");
                         goto fail_cleanup;
@@ -917,7 +930,7 @@ int phub_init_ex(phub_job** out, int num_workers, int num_keys, const int64_t* k
                     if (ph == 0) j->resident_bytes += elems * elem_state_bytes;
                     if (ph == 1)
                         j->loads.push_back(phub::tile_load(
-                            dt, size_t(g) * (2 * size_t(j->bins) + 1), j->bins,
+                            dt, size_t(s) * (2 * size_t(j->bins) + 1), j->bins,
                             int64_t(cus) * (phub::kBlockThreads / 64)));
                     if (ph == 1 && j->dynamic) {
                         // the streamed full tiles become the group's pool, in
@@ -938,8 +951,8 @@ int phub_init_ex(phub_job** out, int num_workers, int num_keys, const int64_t* k
         const std::vector<int32_t>& tile_begin = dt.tile_begin;
         const std::vector<int32_t>& rem_begin = dt.rem_begin;
         std::vector<phub::WaveHead> heads;
-        for (int g = 0; g < j->num_rgroups; ++g)
-            phub::append_wave_heads(dt, size_t(g) * (2 * size_t(j->bins) + 1), j->bins, &heads);
+        for (int s = 0; s < j->num_schedules(); ++s)
+            phub::append_wave_heads(dt, size_t(s) * (2 * size_t(j->bins) + 1), j->bins, &heads);
         j->num_tiles = int64_t(dtiles.size());
         j->num_rems = int64_t(drems.size());
         const size_t tile_bytes = std::max<size_t>(dtiles.size(), 1) * sizeof(phub::DevTile);
