@@ -1,10 +1,12 @@
 """Builds the HIP libraries in-tree for gfx950: ``libphub.so`` (the
 exchange step and its C interface) and ``libphub_probe.so`` (the bandwidth
-probe that the benchmark times beside the step).
+probe that the benchmark times beside the step, and a check of the device's
+square root).
 
-Every source is compiled by hipcc with contraction off, no fast-math and
-subnormals kept, so that the kernel performs exactly the fp32 operations
-the step defines; packed fp32 instructions are disabled.
+Every source is compiled by hipcc with contraction off, no fast-math,
+subnormals kept, and divisions and roots correctly rounded, so that the
+kernel performs exactly the fp32 operations the step defines; packed fp32
+instructions are disabled.
 """
 
 from __future__ import annotations
@@ -25,7 +27,7 @@ PROBE_LIB = os.path.join(PKG, "libphub_probe.so")
 # Ablation build: the gradients loaded cache-allocating (run it with
 # bench.py --library); not built by default.
 GRADIENTS_CACHED_LIB = os.path.join(PKG, "libphub_gradients_cached.so")
-PROBE_SOURCES = ["probe.hip"]
+PROBE_SOURCES = ["probe.hip", "roots.hip"]
 
 SOURCES = ["plan.cpp", "phub_api.cpp", "fused_step.hip", "fused_stream.hip", "fused_many.hip",
            "fused_many_shared.hip", "put_pointers.hip", "step_noalloc.hip"]
@@ -46,6 +48,7 @@ FLAGS = [
     "-ffp-contract=off",
     "-fno-fast-math",
     "-fno-gpu-flush-denormals-to-zero",
+    "-fhip-fp32-correctly-rounded-divide-sqrt",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall",
 ]

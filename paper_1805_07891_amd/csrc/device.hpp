@@ -27,7 +27,8 @@ constexpr int kStates = OPT == kOptSgd ? 1 : (OPT == kOptAdam ? 3 : 2);
 // neighbours have at most 25 significant bits, so their squares are exact in
 // double and comparing x with them decides (a float's square root is never
 // a midpoint, so there are no ties).  The compiler's own sequence for
-// __builtin_sqrtf gives the same bits for all 2^32 inputs, in half the
+// __builtin_sqrtf is correctly rounded too with the flag that the build
+// sets, for all 2^32 inputs (roots.hip checks both), in half the
 // instructions.  The streamed walk uses that (Adam with 16 and 33 workers
 // +2.8 and +0.7 points); the piece-by-piece walks, whose load windows were
 // tuned with the longer one, ran 0.3 to 3.6 points below without it (1 to 6
