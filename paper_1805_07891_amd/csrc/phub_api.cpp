@@ -790,6 +790,10 @@ int phub_init_ex(phub_job** out, int num_workers, int num_keys, const int64_t* k
     {
         const int groups = workgroups > 0 ? workgroups : cus * PHUB_GROUPS_PER_CU;
         const int bins = groups * (phub::kBlockThreads / 64);
+        // the pool walk exists in the fixed-N fused kernels only; others run as LPT
+        j->dynamic = schedule == PHUB_SCHEDULE_DYNAMIC && !unfused &&
+                     phub::takes_tile_pool(num_workers, j->opt);
+        const bool split = schedule == PHUB_SCHEDULE_SPLIT;
         std::string err;
         try {
             plans.resize(size_t(j->num_schedules()) * 2);
@@ -823,7 +827,7 @@ int phub_init_ex(phub_job** out, int num_workers, int num_keys, const int64_t* k
                         // -> 19.4; 6.4 M in 40, 8 workers 52.6 -> 50.8;
                         // 25.6 M in 161, 8 workers 189.4 -> 187.3, 16
                         // workers 309.9 -> 305.6; others level.
-                        if (schedule == PHUB_SCHEDULE_LPT && !whole_chunks &&
+                        if (!split && !j->dynamic && !whole_chunks &&
                             chunk_bytes >= phub::kTileElems * int64_t(sizeof(float)))
                             err = phub::build_dealt(int(vk.size()), elems.data(), phub::kTileElems,
                                                     (num_workers + 2 * int64_t(j->num_states)) * 4,
@@ -833,9 +837,7 @@ int phub_init_ex(phub_job** out, int num_workers, int num_keys, const int64_t* k
                         else
                             err = phub::build_plan(num_workers, int(vk.size()), elems.data(),
                                                    chunk_bytes,
-                                                   schedule == PHUB_SCHEDULE_DYNAMIC
-                                                       ? phub::kScheduleLpt
-                                                       : schedule,
+                                                   split ? phub::kScheduleSplit : phub::kScheduleLpt,
                                                    bins, whole_chunks ? 0 : kLptItemsPerBin * bins,
                                                    &plan);
                     } else {
@@ -864,9 +866,7 @@ int phub_init_ex(phub_job** out, int num_workers, int num_keys, const int64_t* k
         j->bins = bins;
     }
     j->schedule = schedule;
-    // the pool walk exists in the fixed-N fused kernels only
-    j->dynamic = schedule == PHUB_SCHEDULE_DYNAMIC && !unfused && j->groups > 0 &&
-                 phub::takes_tile_pool(num_workers, j->opt);
+    j->dynamic = j->dynamic && j->groups > 0;
     const int num_states = j->num_states;
 
 #define PHUB_TRY(call, what)                 \
