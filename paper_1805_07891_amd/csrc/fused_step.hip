@@ -382,10 +382,8 @@ hipError_t launch_pull(const StepParams& p, int grid, hipStream_t stream) {
     static_assert(has_fixed_kernel(20) && has_fixed_kernel(24) && has_fixed_kernel(32),
                   "the larger counts below");
     if constexpr (!PULL)  // (the streamed walk takes no tile pool)
-        if (p.pool_count == 0 && has_fixed_kernel(p.num_workers) &&
-            stream_block(p.num_workers, kStates<OPT>) &&
-            p.load.streamed >=
-                int64_t(kStreamMinTiles[kStates<OPT> - 1]) * grid * kWavesPerBlock)
+        if (p.pool_count == 0 &&
+            takes_stream(p.num_workers, kStates<OPT>, p.load, int64_t(grid) * kWavesPerBlock))
             return launch_stream<OPT>(p, grid, stream);
     switch (p.num_workers) {
         case 1: return launch_one<1, OPT, PULL>(p, grid, stream);

@@ -1,4 +1,5 @@
-// The choice of the any-N kernel on the host.  Exit status 0 when all hold.
+// The choice of the any-N kernel and of the stream walk of the fixed-N kernels
+// on the host.  Exit status 0 when all hold.
 #include <cstdio>
 #include <cstdlib>
 #include <utility>
@@ -63,5 +64,23 @@ int main() {
         check(any_kernel(64, dealt({4000000}, 4 * grid, waves)) == kAnyBatches, "small grid", grid);
     for (int grid : {192, 224, 256, 512})
         check(any_kernel(64, dealt({4000000}, 4 * grid, waves)) == kAnyStream, "grid", grid);
+    // the fixed-N kernels' stream walk: enough streamed tiles for the launch's
+    // waves, and for momentum and plain SGD evenly spread
+    for (int s : {1, 2, 3})
+        for (int n = 1; n <= 40; ++n) {
+            const bool stream = has_fixed_kernel(n) && stream_block(n, s) != 0;
+            const int64_t least = kStreamMinTiles[s - 1];
+            for (int64_t g : {4, 12, 1024}) {
+                check(takes_stream(n, s, {least * g, 0, least, waves}, g) == stream, "least", n, s);
+                check(!takes_stream(n, s, {least * g - 1, 0, least, waves}, g), "fewer", n, s);
+                check(takes_stream(n, s, {20 * g, 0, 26, waves}, g) == stream, "even", n, s);
+                check(takes_stream(n, s, {20 * g, 0, 27, waves}, g) == (stream && s == 3), "uneven", n, s);
+                check(!takes_stream(n, s, {0, 90 * g, 90, waves}, g), "cached", n, s);
+            }
+            // what phub_init deals is even, cut or not
+            for (int64_t elems : {4200000, 5000000, 6400000, 25557032})
+                check(takes_stream(n, s, dealt({elems, 77, 301}, int(waves), waves), waves) == stream,
+                      "dealt", n, elems);
+        }
     return 0;
 }
