@@ -77,6 +77,12 @@ int main() {
                 check(takes_stream(n, s, {20 * g, 0, 27, waves}, g) == (stream && s == 3), "uneven", n, s);
                 check(!takes_stream(n, s, {0, 90 * g, 90, waves}, g), "cached", n, s);
             }
+            // the grids on which tests/test_gpu_stream_kernels.py means the stream
+            // walk, and those on which it means the window over a tile
+            const std::vector<int64_t> keys = {5, 1024 * 37 + 3, 70001, 1024 * 11, 4097, 1, 1024 * 6};
+            check(takes_stream(n, s, dealt(keys, 4, waves), 4) == stream, "one workgroup", n, s);
+            const int few = s == 3 ? 64 : 40;
+            check(!takes_stream(n, s, dealt(keys, few, waves), few), "few tiles", n, s);
             // what phub_init deals is even, cut or not
             for (int64_t elems : {4200000, 5000000, 6400000, 25557032})
                 check(takes_stream(n, s, dealt({elems, 77, 301}, int(waves), waves), waves) == stream,
