@@ -58,17 +58,6 @@ int phub_probe_mixed(const float *const *read_streams, int nread, float *const *
                      int nrw, int64_t elems_each, int grid, float sentinel, float *sink,
                      void *hip_stream);
 
-/*
- * phub_probe_roots - enqueue a check of the fp32 square roots that Adam's
- * update takes (the compiler's, and the one with its rounding checked)
- * against the correctly rounded root, for all 2^32 bit patterns.
- *   wrong   device array of two counters, caller-owned and cleared by the
- *           caller: inputs where the compiler's root differs are added to
- *           the first, those where the checked root does to the second.
- * Returns 0, -1 if wrong is NULL, or the HIP error code of the launch.
- */
-int phub_probe_roots(uint64_t *wrong, void *hip_stream);
-
 /* Elements per probe tile: elems_each must be a multiple of it. */
 int phub_probe_tile_elems(void);
 

@@ -1,7 +1,7 @@
 """Builds the HIP libraries in-tree for gfx950: ``libphub.so`` (the
 exchange step and its C interface) and ``libphub_probe.so`` (the bandwidth
-probe that the benchmark times beside the step, and a check of the device's
-square root).
+probe that the benchmark times beside the step) and ``libphub_roots.so`` (a
+check of the device's square roots).
 
 Every source is compiled by hipcc with contraction off, no fast-math,
 subnormals kept, and divisions and roots correctly rounded, so that the
@@ -27,7 +27,9 @@ PROBE_LIB = os.path.join(PKG, "libphub_probe.so")
 # Ablation build: the gradients loaded cache-allocating (run it with
 # bench.py --library); not built by default.
 GRADIENTS_CACHED_LIB = os.path.join(PKG, "libphub_gradients_cached.so")
-PROBE_SOURCES = ["probe.hip", "roots.hip"]
+PROBE_SOURCES = ["probe.hip"]
+ROOTS_LIB = os.path.join(PKG, "libphub_roots.so")
+ROOTS_SOURCES = ["roots.hip"]
 
 SOURCES = ["plan.cpp", "phub_api.cpp", "fused_step.hip", "fused_stream.hip", "fused_many.hip",
            "fused_many_shared.hip", "put_pointers.hip", "step_noalloc.hip"]
@@ -81,9 +83,10 @@ def build(out: str = LIB, defines: Sequence[str] = (), extra: Sequence[str] = ()
     return out
 
 
-def build_probe(out: str = PROBE_LIB, verbose: bool = False) -> str:
+def build_probe(out: str = PROBE_LIB, verbose: bool = False,
+                sources: Sequence[str] = PROBE_SOURCES) -> str:
     """Compile the bandwidth probe library; returns its path."""
-    srcs = [os.path.join(CSRC, s) for s in PROBE_SOURCES]
+    srcs = [os.path.join(CSRC, s) for s in sources]
     tmp = out + ".tmp"
     cmd = [HIPCC, *FLAGS, f"-I{INCLUDE}", *srcs, "-o", tmp]
     if verbose:
@@ -108,6 +111,7 @@ def device_assembly(out: str, source: str = "fused_step.hip", defines: Sequence[
 def build_all(verbose: bool = False) -> None:
     build(verbose=verbose)
     build_probe(verbose=verbose)
+    build_probe(ROOTS_LIB, verbose, ROOTS_SOURCES)
 
 
 def build_gradients_cached(verbose: bool = False) -> str:

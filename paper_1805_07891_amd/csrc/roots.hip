@@ -6,7 +6,6 @@
 #include <cstdint>
 
 #include "device.hpp"
-#include "phub_probe.h"
 
 namespace {
 
@@ -16,7 +15,7 @@ constexpr int kRootThreads = 256, kRootGrid = 1024;
 // root rounded to fp32 is the correctly rounded fp32 root (53 bits are more
 // than twice 24 and two).  wrong[0]: __builtin_sqrtf differs from it;
 // wrong[1]: sqrt_rn does (any NaN is equal to any other).
-__global__ __launch_bounds__(kRootThreads) void probe_roots(unsigned long long* wrong) {
+__global__ __launch_bounds__(kRootThreads) void check_roots(unsigned long long* wrong) {
     uint32_t plain = 0, checked = 0;
     const uint64_t stride = uint64_t(kRootThreads) * kRootGrid;
     for (uint64_t b = uint64_t(blockIdx.x) * kRootThreads + threadIdx.x; b < (uint64_t(1) << 32);
@@ -37,9 +36,14 @@ __global__ __launch_bounds__(kRootThreads) void probe_roots(unsigned long long* 
 
 }  // namespace
 
-extern "C" int phub_probe_roots(uint64_t* wrong, void* hip_stream) {
+// Enqueues the check on hip_stream.  wrong: device array of two counters,
+// cleared by the caller; inputs where the compiler's root differs from the
+// correctly rounded one are added to the first, those where sqrt_rn's does to
+// the second.  Returns 0, -1 if wrong is NULL, or the HIP error code of the
+// launch.
+extern "C" int phub_check_roots(uint64_t* wrong, void* hip_stream) {
     if (!wrong) return -1;
-    hipLaunchKernelGGL(probe_roots, dim3(kRootGrid), dim3(kRootThreads), 0, (hipStream_t)hip_stream,
+    hipLaunchKernelGGL(check_roots, dim3(kRootGrid), dim3(kRootThreads), 0, (hipStream_t)hip_stream,
                        reinterpret_cast<unsigned long long*>(wrong));
     return int(hipGetLastError());
 }

@@ -16,12 +16,12 @@ def test_the_build_asks_for_correctly_rounded_roots():
 @pytest.mark.gpu
 def test_both_roots_are_correctly_rounded_for_every_value():
     import torch
-    probe = ctypes.CDLL(build.PROBE_LIB)
-    probe.phub_probe_roots.argtypes = [ctypes.c_void_p, ctypes.c_void_p]
+    lib = ctypes.CDLL(build.ROOTS_LIB)
+    lib.phub_check_roots.argtypes = [ctypes.c_void_p, ctypes.c_void_p]
     wrong = torch.zeros(2, dtype=torch.int64, device="cuda:0")
     torch.cuda.synchronize()
     print("roots of 2^32 values", flush=True)
-    assert probe.phub_probe_roots(None, None) == -1
-    assert probe.phub_probe_roots(wrong.data_ptr(), None) == 0
+    assert lib.phub_check_roots(None, None) == -1
+    assert lib.phub_check_roots(wrong.data_ptr(), None) == 0
     torch.cuda.synchronize()
     assert wrong.tolist() == [0, 0]
