@@ -913,7 +913,8 @@ int phub_init_ex(phub_job** out, int num_workers, int num_keys, const int64_t* k
         // the streamed ones).  A descriptor's key is the key's row in the
         // pointer table.
         phub::DeviceTables dt;
-        {
+        std::vector<phub::WaveHead> heads;
+        try {
             std::vector<int64_t> row_arena_offset(num_keys);
             for (int r = 0; r < num_keys; ++r) row_arena_offset[r] = j->arena_offset[j->key_of_row[r]];
             for (int s = 0; s < j->num_schedules(); ++s) {
@@ -945,14 +946,17 @@ int phub_init_ex(phub_job** out, int num_workers, int num_keys, const int64_t* k
                     }
                 }
             }
+            for (int s = 0; s < j->num_schedules(); ++s)
+                phub::append_wave_heads(dt, size_t(s) * (2 * size_t(j->bins) + 1), j->bins, &heads);
+            j->pool_launches.assign(j->num_rgroups, 0);
+        } catch (const std::bad_alloc&) {
+            rc = fail(PHUB_ENOMEM, "host allocation of the device tables failed");
+            goto fail_cleanup;
         }
         const std::vector<phub::DevTile>& dtiles = dt.tiles;
         const std::vector<phub::DevRem>& drems = dt.rems;
         const std::vector<int32_t>& tile_begin = dt.tile_begin;
         const std::vector<int32_t>& rem_begin = dt.rem_begin;
-        std::vector<phub::WaveHead> heads;
-        for (int s = 0; s < j->num_schedules(); ++s)
-            phub::append_wave_heads(dt, size_t(s) * (2 * size_t(j->bins) + 1), j->bins, &heads);
         j->num_tiles = int64_t(dtiles.size());
         j->num_rems = int64_t(drems.size());
         const size_t tile_bytes = std::max<size_t>(dtiles.size(), 1) * sizeof(phub::DevTile);
@@ -963,7 +967,6 @@ int phub_init_ex(phub_job** out, int num_workers, int num_keys, const int64_t* k
         const size_t tab_bytes = j->grads.size() * sizeof(const float*);
         const size_t counter_bytes =
             size_t(j->num_rgroups) * kCountersPerGroup * sizeof(unsigned long long);
-        j->pool_launches.assign(j->num_rgroups, 0);
         if (hipMalloc(&j->d_tiles, tile_bytes) != hipSuccess ||
             hipMalloc(&j->d_tile_begin, tb_bytes) != hipSuccess ||
             hipMalloc(&j->d_rems, rem_bytes) != hipSuccess ||

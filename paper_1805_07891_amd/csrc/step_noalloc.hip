@@ -246,7 +246,12 @@ extern "C" int phub_step_noalloc(int num_workers, int num_keys, const int64_t* k
         return report_error(PHUB_EINVAL, "lr, momentum and weight_decay must be finite");
     if (!grads) return report_error(PHUB_EINVAL, "grads is NULL");
     // the arena layout of a job's state: key slices padded to 64 elements
-    std::vector<int64_t> arena_offset(num_keys);
+    std::vector<int64_t> arena_offset;
+    try {
+        arena_offset.resize(num_keys);
+    } catch (const std::bad_alloc&) {
+        return report_error(PHUB_ENOMEM, "host allocation of the key offsets failed");
+    }
     int64_t arena_elems = 0;
     for (int k = 0; k < num_keys; ++k) {
         if (key_elems[k] >= phub::kMaxDeviceKeyElems)
