@@ -103,28 +103,6 @@ constexpr bool burst_write_back(int num_workers, int num_states) {
            num_workers >= kBurstMinWorkers[num_states - 1];
 }
 
-// Whole rounds of full tiles from which a dealt schedule (build_dealt) cuts
-// the tiles left over from the last one evenly over the waves; negative:
-// never.  Cut where the state is streamed and written back in bursts.
-// Measured on MI355X, whole -> cut: 8 workers over 1.2 M parameters 12.2 ->
-// 10.8 us, over 4.7 M 39.3 -> 37.4, 16 over 2.4 M 34.7 -> 32.4, pushpull with
-// 8 over 1.2 M 23.0 -> 20.7.  The kernels without bursts run a second tile on
-// in the load window of the first, and a piece costs its own trip to memory:
-// 2 workers over 1.2 M 6.8 -> 7.6 us, 4 over 1.2 M 8.3 -> 9.1, Adam with 8
-// over 1.7 M 19.4 -> 20.4, cached state with 8 over 1.2 M 11.4 -> 12.5; four
-// jobs at once up to 25% (1 worker, Adam, 1.7 M each 37 -> 46).  The any-N
-// stream's piece is a walk of its own (17 workers over 1.4 M 23.2 -> 24.4):
-// below eight rounds 0 to 5% slower, beyond within 1% either way, alone up to
-// 1% faster (64 workers over 25.6 M 1024 -> 1016).  Below one round a cut
-// gives a lone job up to 7%, and costs small jobs that run at the same time
-// about as much (two of 8 workers over 0.6 M 9.3 -> 10.2 us, one 6.7 -> 6.4),
-// since each is then on every compute unit.
-constexpr int cut_rounds(int num_workers, int num_states, bool streamed, bool unfused) {
-    if (!streamed || unfused) return -1;
-    if (!has_fixed_kernel(num_workers)) return 8;
-    return burst_write_back(num_workers, num_states) ? 0 : -1;
-}
-
 // The burst write-back's stash: LDS per wave (the compute unit's 160 KB
 // over its four waves), and how many tiles of state it holds for a job
 // with num_states state arrays (a tile is 4 KB per array and wave).
@@ -211,8 +189,9 @@ struct OptArgs {
 struct TileLoad {
     int64_t streamed;  // full tiles of all streamed bins
     int64_t resident;  // full tiles of all cache-resident bins
-    int64_t busiest;   // the most one wave has, of both
-    int64_t waves;     // one per SIMD of the whole device, launched or not
+    int64_t rems;      // remainders of all bins
+    int64_t busiest;   // the most full tiles one wave has, of both
+    int64_t waves;     // the launch's, at most one per SIMD of the device
 };
 
 // The schedule of one launch has two bins per wave.  With
@@ -334,6 +313,39 @@ constexpr int stream_block(int num_workers, int num_states) {
     return num_workers > kMaxFixedWorkers ? 6 : kStreamBlock[num_states - 1][num_workers - 1];
 }
 
+// When a dealt schedule (build_dealt) cuts the tiles left over from the last
+// whole round evenly over the waves.  Measured on MI355X, whole -> cut.
+// From one round on, where the state is streamed and written back in bursts:
+// 8 workers over 1.2 M parameters 12.2 -> 10.8 us, over 4.7 M 39.3 -> 37.4, 16
+// over 2.4 M 34.7 -> 32.4, pushpull with 8 over 1.2 M 23.0 -> 20.7, Adam with
+// 7 over 2.4 M 25.9 -> 24.3.  Without bursts a wave runs a second tile on in
+// the load window of the first, and a piece costs its own trip to memory: 2
+// workers over 1.2 M 6.8 -> 7.6 us, 4 over 1.2 M 8.3 -> 9.1, Adam with 8 over
+// 1.7 M 19.4 -> 20.4, cached state with 8 over 1.2 M 11.4 -> 12.5; four jobs at
+// once up to 25% (1 worker, Adam, 1.7 M each 37 -> 46).  The any-N stream's
+// piece is a walk of its own (17 workers over 1.4 M 23.2 -> 24.4): below eight
+// rounds 0 to 5% slower, beyond within 1% either way, alone up to 1% faster
+// (64 workers over 25.6 M 1024 -> 1016).
+// Below one round most waves would have no tile.  Pieces of up to half a tile
+// gain up to 1.6 times (Adam with 8 over 0.4 M 8.4 -> 6.5 us, 16 workers over
+// 0.4 M 9.2 -> 6.3, 64 over 0.02 M 15.0 -> 9.7) and cost four jobs at once 0
+// to 6%, at worst 19; longer ones gain 0 to 7% (cached
+// state up to 15) with as many workers as bursts take, else less than they
+// cost jobs that run at the same time (two of 8 workers over 0.6 M each 9.3 ->
+// 10.2 us).
+constexpr Cut cut_rule(int num_workers, int num_states, bool streamed, bool unfused) {
+    const bool fixed = has_fixed_kernel(num_workers) && !unfused;
+    const bool burst = fixed && burst_write_back(num_workers, num_states);
+    Cut cut;
+    cut.below_one_round = burst ? kTileElems * 3 / 4 : kTileElems / 2;
+    cut.rounds = !streamed || unfused                              ? -1
+                 : !fixed                                          ? 8
+                 : burst                                           ? 0
+                 : stream_block(num_workers, num_states) != 0 ? kStreamMinTiles[num_states - 1]
+                                                                   : -1;
+    return cut;
+}
+
 // Whether a step of a fixed-N kernel walks its streamed tiles as one stream
 // (no model buffers; grid_waves: the launch's waves).  Not where chunks kept
 // whole leave waves idle: over 5 M parameters in 32 KB chunks (five waves of
@@ -354,15 +366,21 @@ enum AnyKernel { kAnyBatches, kAnyStream, kAnyStreamShared };
 constexpr int kManyBlock = 6;  // loads of a block
 
 // The stream walk keeps six loads in flight per wave, a batch thirty-two: the
-// stream is the faster where the chip's waves share the work, the batches
-// where a few of them have most of it (chunks kept whole, a grid of few
-// workgroups), and each waits for memory's latency.  The share of the chip
-// that is busy until the busiest wave ends, batches -> stream (17 to 64
-// workers, the three optimizers): 1/8 0.75-0.86 of the speed, 1/4 0.81-0.90,
-// 1/2 0.92-1.0, 5/8 0.92-1.04, 3/4 1.01-1.10, 7/8 1.07-1.14.  Up to two tiles
-// a wave the schedules that phub_init deals are never uneven in that sense.
+// stream is the faster where the launch's waves share the work, the batches
+// where a few of them have most of it (chunks kept whole) and each waits for
+// memory's latency.  The share of the waves that is busy until the busiest
+// ends, batches -> stream (17 to 64 workers, the three optimizers): 1/8
+// 0.78-0.85 of the speed, 1/4 0.81-0.88, 1/2 0.94-1.0, 5/8 0.92-0.99, 3/4
+// 1.01-1.07, 7/8 1.09-1.14.  Up to two tiles a wave the schedules that
+// phub_init deals are never uneven in that sense; and many small keys are the
+// stream's (31 workers over 0.5 M parameters in 443 keys, chunks kept whole,
+// 190 -> 145 us).  A grid of few workgroups is not counted: it is for tenants
+// to share the chip, where the stream is the faster (four of 21 workers over
+// 25.6 M on 64 workgroups each 2511 -> 2244 us, though one alone on 64, 94
+// workers over 1.9 M, 272 -> 300).
 constexpr bool few_waves_busy(const TileLoad& l) {
-    return l.busiest > 2 && 8 * (l.streamed + l.resident) <= 5 * l.busiest * l.waves;
+    const int64_t tiles = l.streamed + l.resident;
+    return l.busiest > 2 && tiles >= l.rems && 8 * tiles <= 5 * l.busiest * l.waves;
 }
 
 // State that is cached needs no bursts.  Up to three tiles a wave the stream
@@ -372,7 +390,8 @@ constexpr bool few_waves_busy(const TileLoad& l) {
 // faster.  Batches -> stream, the speed of one job and of four at once (17 to
 // 64 workers, the three optimizers): 1 tile 1.32-1.44 and 0.99-1.15, 2 tiles
 // 1.11-1.22 and 0.95-1.02, 3 tiles 0.99-1.16 and 0.98-1.07, 4 tiles
-// 0.96-1.09 and 0.98-1.05, 25.6 M parameters with 21 0.97 (one job).
+// 0.96-1.09 and 0.98-1.05, 25.6 M parameters with 21 0.97 (one job).  (Tiles
+// per wave of the device: a larger grid splits the same work.)
 constexpr int64_t kSharedTiles = 3;
 constexpr int kSharedStashBytesPerWave = 16 * 1024;
 constexpr int shared_stash_tiles(int num_states) {
@@ -382,7 +401,8 @@ constexpr int shared_stash_tiles(int num_states) {
 constexpr AnyKernel any_kernel(int num_workers, const TileLoad& load) {
     if (num_workers <= kManyBlock || few_waves_busy(load)) return kAnyBatches;
     if (load.resident >= load.streamed)  // (none of either: remainders only)
-        return load.busiest <= kSharedTiles ? kAnyStreamShared : kAnyBatches;
+        return load.resident + load.streamed <= kSharedTiles * load.waves ? kAnyStreamShared
+                                                                          : kAnyBatches;
     return kAnyStream;
 }
 

@@ -503,7 +503,8 @@ int64_t append_device_tables(const Plan& plan, const std::vector<VirtualKey>& vk
 
 TileLoad tile_load(const DeviceTables& dt, size_t block, int bins, int64_t waves) {
     const int32_t* tb = dt.tile_begin.data() + block;
-    TileLoad l{tb[2 * bins] - tb[bins], tb[bins] - tb[0], 0, waves};
+    const int32_t* rb = dt.rem_begin.data() + block;
+    TileLoad l{tb[2 * bins] - tb[bins], tb[bins] - tb[0], rb[2 * bins] - rb[0], 0, waves};
     for (int w = 0; w < bins; ++w)
         l.busiest = std::max<int64_t>(l.busiest, tb[w + 1] - tb[w] + tb[bins + w + 1] - tb[bins + w]);
     return l;
@@ -832,8 +833,8 @@ int phub_init_ex(phub_job** out, int num_workers, int num_keys, const int64_t* k
                             err = phub::build_dealt(int(vk.size()), elems.data(), phub::kTileElems,
                                                     (num_workers + 2 * int64_t(j->num_states)) * 4,
                                                     bins, &plan,
-                                                    phub::cut_rounds(num_workers, j->num_states,
-                                                                     ph == 1, unfused));
+                                                    phub::cut_rule(num_workers, j->num_states,
+                                                                   ph == 1, unfused));
                         else
                             err = phub::build_plan(num_workers, int(vk.size()), elems.data(),
                                                    chunk_bytes,
@@ -932,7 +933,7 @@ int phub_init_ex(phub_job** out, int num_workers, int num_keys, const int64_t* k
                     if (ph == 1)
                         j->loads.push_back(phub::tile_load(
                             dt, size_t(s) * (2 * size_t(j->bins) + 1), j->bins,
-                            int64_t(cus) * (phub::kBlockThreads / 64)));
+                            std::min<int64_t>(j->bins, int64_t(cus) * (phub::kBlockThreads / 64))));
                     if (ph == 1 && j->dynamic) {
                         // the streamed full tiles become the group's pool, in
                         // address order; its bins keep their remainders only

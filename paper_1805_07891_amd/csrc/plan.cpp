@@ -243,7 +243,7 @@ std::string build_plan(int num_workers, int num_keys, const int64_t* key_elems,
 }
 
 std::string build_dealt(int num_keys, const int64_t* key_elems, int64_t tile_elems,
-                        int64_t bytes_per_elem, int num_bins, Plan* out, int cut_rounds) {
+                        int64_t bytes_per_elem, int num_bins, Plan* out, Cut cut) {
     if (num_bins < 1) return "num_bins must be >= 1, got " + std::to_string(num_bins);
     if (tile_elems < 4 * kPieceAlign || tile_elems % kPieceAlign != 0) return "bad tile size";
     out->segments.clear();
@@ -257,14 +257,15 @@ std::string build_dealt(int num_keys, const int64_t* key_elems, int64_t tile_ele
     }
     // Tiles [0, whole) are dealt in turn; the leftover [whole, tiles) is cut
     // into pieces of `piece` elements, one for each bin that need not take a
-    // remainder, unless a piece would be nearly a tile.
+    // remainder, unless a piece would be too long.
     int64_t whole = tiles - tiles % num_bins;
     int64_t piece = 0;
-    if (cut_rounds >= 0 && tiles / num_bins >= cut_rounds && whole < tiles && rems < num_bins) {
+    const bool wanted = whole == 0 || (cut.rounds >= 0 && tiles / num_bins >= cut.rounds);
+    if (wanted && whole < tiles && rems < num_bins) {
         const int64_t left = (tiles - whole) * tile_elems, bins = num_bins - rems;
         piece = (left + bins - 1) / bins;
         piece = std::max((piece + kPieceAlign - 1) / kPieceAlign * kPieceAlign, 4 * kPieceAlign);
-        if (piece > tile_elems * 3 / 4) piece = 0;
+        if (piece > (whole == 0 ? cut.below_one_round : tile_elems * 3 / 4)) piece = 0;
     }
     if (piece == 0) whole = tiles;
 

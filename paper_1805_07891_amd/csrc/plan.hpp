@@ -58,19 +58,27 @@ std::string build_plan(int num_workers, int num_keys, const int64_t* key_elems,
                        int64_t chunk_bytes, int schedule, int num_bins, int min_items,
                        Plan* out);
 
+// When build_dealt cuts leftover tiles: with fewer tiles than bins, where a
+// piece is at most below_one_round elements; else from `rounds` whole rounds
+// on (negative: never), where a piece is at most three quarters of a tile.
+struct Cut {
+    int rounds = 0;
+    int64_t below_one_round = 768;
+};
+
 // The schedule that phub_init runs for PHUB_SCHEDULE_LPT (kept apart from
 // build_plan, whose schedule is part of the interface): the same balanced
 // partition, dealt at the granularity the kernels work in.  Every key's full
 // tiles of tile_elems elements go to the bins in turn (which is what the
 // longest-processing-time-first rule does with equal items), then the keys'
 // remainders largest first to the least loaded bin; small keys are not
-// bundled (a wave walks its remainders one after another).  Where
-// there are cut_rounds whole rounds of tiles (negative: never) and few enough
-// are left over, those are cut into equal pieces so that every bin gets one.
-// bytes_per_elem: what the step moves per element.
+// bundled (a wave walks its remainders one after another).  The
+// tiles left over from the last whole round are cut into equal pieces so that
+// every bin gets one, as `cut` says.  bytes_per_elem: what the step moves per
+// element.
 std::string build_dealt(int num_keys, const int64_t* key_elems, int64_t tile_elems,
                         int64_t bytes_per_elem, int num_bins, Plan* out,
-                        int cut_rounds = 0);
+                        Cut cut = {});
 
 // Full tiles of tile_elems elements and remainders that the LPT schedule's
 // segments would be cut into (the arguments as build_plan's), counted key by

@@ -393,7 +393,7 @@ extern "C" int phub_step_noalloc(int num_workers, int num_keys, const int64_t* k
 
     phub::StepParams p{};
     p.heads = d_heads;
-    p.load = {num_tiles, 0, (int64_t(num_tiles) + bins - 1) / bins, bins};
+    p.load = {num_tiles, 0, num_rems, (int64_t(num_tiles) + bins - 1) / bins, bins};
     p.tiles = d_tiles;
     p.rems = d_rems;
     p.grads = reinterpret_cast<const float* const*>(d_ptrs);

@@ -22,16 +22,23 @@ def test_rule_and_plans(tmp_path):
     assert out.returncode == 0, out.stderr
 
 
+# below one whole round on 8 waves, by the tiles left over: a piece is 3/7 and
+# 4/7 of a tile (to 64 elements); then two and eight whole rounds and four tiles
+LEFT = (3, 4, 20, 68)
+BURST, PIECEWISE, CACHED = (3, 4, 20, 68), (3,), (3, 4)
+
+
 @pytest.mark.gpu
-@pytest.mark.parametrize("n,opt,kw,rounds", [
-    (8, None, {}, 0), (6, "sgd", {}, 0), (14, "adam", {}, 0), (32, None, {}, 0),
-    (1, "adam", {}, None), (4, None, {}, None), (8, "adam", {}, None),
-    (17, None, {"resident_bytes": 0}, 8), (21, "adam", {"resident_bytes": 0}, 8),
-    (8, None, {"resident_bytes": 1 << 28}, None), (8, None, {"unfused": True}, None)])
-def test_segments_of_jobs(n, opt, kw, rounds):
+@pytest.mark.parametrize("n,opt,kw,cut", [
+    (8, None, {}, BURST), (6, "sgd", {}, BURST), (14, "adam", {}, BURST), (32, None, {}, BURST),
+    (1, "adam", {}, PIECEWISE), (4, None, {}, PIECEWISE), (8, "adam", {}, PIECEWISE),
+    (8, "adam", {"resident_bytes": 0}, (3, 20, 68)),
+    (17, None, {"resident_bytes": 0}, (3, 68)), (21, "adam", {"resident_bytes": 0}, (3, 68)),
+    (8, None, {"resident_bytes": 1 << 28}, CACHED), (8, None, {"unfused": True}, PIECEWISE)])
+def test_segments_of_jobs(n, opt, kw, cut):
     from paper_1805_07891_amd.job import TorchJob
     print("segments", n, opt, kw, flush=True)
-    for tiles in (4, 20, 68):  # on 8 waves: none, two and eight whole rounds, four tiles left over
+    for tiles in LEFT:
         job = TorchJob(Job("cut", n, (tiles * 1024 + 3,)), "cuda:0", workgroups=2, optimizer=opt, **kw)
-        assert (job.info()[2] > tiles + 1) == (rounds is not None and tiles // 8 >= rounds), tiles
+        assert (job.info()[2] > tiles + 1) == (tiles in cut), tiles
         job.destroy()

@@ -30,7 +30,7 @@ def test_dealt_plans(tmp_path):
 @pytest.mark.parametrize("n,opt,tiles,resident", [
     # on 8 waves: no whole round, one leftover tile (cut to 256 elements),
     # pieces of 320 and 640, too many leftover tiles to cut, two bins' state;
-    # 2 to 4 workers and any-N jobs leave theirs whole
+    # above one round 2 to 4 workers and any-N jobs leave theirs whole
     (8, None, 1, 0), (2, None, 9, 0), (8, None, 10, 0), (3, "adam", 13, 0), (16, "sgd", 15, 0),
     (4, None, 29, 8 * 9000), (20, None, 9, 0), (24, "adam", 11, 0), (33, None, 10, 0),
     (17, "sgd", 5, 4 * 3000)])

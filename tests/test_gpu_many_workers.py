@@ -1,10 +1,8 @@
 """GPU parity of the kernels for worker counts without a kernel of their own
 (17 and more): every block size and filling of the last block, more workers
-than one load of 64 covers, keys of every remainder class, grids of one and
-two workgroups (a wave walks many tiles, in batches) and the whole one (the
-stream walk; test_gpu_many_stream.py has it over many tiles), state cached or
-streamed or cut inside a key; bit-exact against the CPU oracle over two
-steps."""
+than one load of 64 covers, keys of every remainder class, grids small
+enough that a wave walks many tiles, state cached or streamed or cut inside
+a key; bit-exact against the CPU oracle over two steps."""
 
 import sys
 
