@@ -322,27 +322,31 @@ constexpr int stream_block(int num_workers, int num_states) {
 // the load window of the first, and a piece costs its own trip to memory: 2
 // workers over 1.2 M 6.8 -> 7.6 us, 4 over 1.2 M 8.3 -> 9.1, Adam with 8 over
 // 1.7 M 19.4 -> 20.4, cached state with 8 over 1.2 M 11.4 -> 12.5; four jobs at
-// once up to 25% (1 worker, Adam, 1.7 M each 37 -> 46).  The any-N stream's
-// piece is a walk of its own (17 workers over 1.4 M 23.2 -> 24.4): below eight
-// rounds 0 to 5% slower, beyond within 1% either way, alone up to 1% faster
-// (64 workers over 25.6 M 1024 -> 1016).
+// once up to 25% (1 worker, Adam, 1.7 M each 37 -> 46).  From 16 rounds on it
+// is level to 2% faster, pushpull 1 to 3%, four jobs at once within 1%; with as
+// many workers as bursts take, cached state reaches that at 4 rounds (pushpull
+// with 8 over 5.6 M 77.0 -> 74.0).  The any-N stream's piece is a walk of its
+// own (17 workers over 1.4 M 23.2 -> 24.4): below eight rounds 0 to 5% slower,
+// beyond within 1% either way, alone up to 1% faster (64 workers over 25.6 M
+// 1024 -> 1016).
 // Below one round most waves would have no tile.  Pieces of up to half a tile
 // gain up to 1.6 times (Adam with 8 over 0.4 M 8.4 -> 6.5 us, 16 workers over
 // 0.4 M 9.2 -> 6.3, 64 over 0.02 M 15.0 -> 9.7) and cost four jobs at once 0
-// to 6%, at worst 19; longer ones gain 0 to 7% (cached
-// state up to 15) with as many workers as bursts take, else less than they
-// cost jobs that run at the same time (two of 8 workers over 0.6 M each 9.3 ->
-// 10.2 us).
+// to 6%, at worst 19; longer ones gain 0 to 7% (cached state up to 15) with as
+// many workers as bursts take, else less than they cost jobs that run at the
+// same time (two of 8 workers over 0.6 M each 9.3 -> 10.2 us).
 constexpr Cut cut_rule(int num_workers, int num_states, bool streamed, bool unfused) {
     const bool fixed = has_fixed_kernel(num_workers) && !unfused;
     const bool burst = fixed && burst_write_back(num_workers, num_states);
     Cut cut;
     cut.below_one_round = burst ? kTileElems * 3 / 4 : kTileElems / 2;
-    cut.rounds = !streamed || unfused                              ? -1
-                 : !fixed                                          ? 8
-                 : burst                                           ? 0
-                 : stream_block(num_workers, num_states) != 0 ? kStreamMinTiles[num_states - 1]
-                                                                   : -1;
+    cut.rounds = 16;
+    if (burst)
+        cut.rounds = streamed ? 0 : 4;
+    else if (streamed && fixed && stream_block(num_workers, num_states) != 0)
+        cut.rounds = kStreamMinTiles[num_states - 1];
+    else if (streamed && !unfused && !fixed)
+        cut.rounds = 8;
     return cut;
 }
 

@@ -260,8 +260,7 @@ std::string build_dealt(int num_keys, const int64_t* key_elems, int64_t tile_ele
     // remainder, unless a piece would be too long.
     int64_t whole = tiles - tiles % num_bins;
     int64_t piece = 0;
-    const bool wanted = whole == 0 || (cut.rounds >= 0 && tiles / num_bins >= cut.rounds);
-    if (wanted && whole < tiles && rems < num_bins) {
+    if ((whole == 0 || tiles / num_bins >= cut.rounds) && whole < tiles && rems < num_bins) {
         const int64_t left = (tiles - whole) * tile_elems, bins = num_bins - rems;
         piece = (left + bins - 1) / bins;
         piece = std::max((piece + kPieceAlign - 1) / kPieceAlign * kPieceAlign, 4 * kPieceAlign);

@@ -60,7 +60,7 @@ std::string build_plan(int num_workers, int num_keys, const int64_t* key_elems,
 
 // When build_dealt cuts leftover tiles: with fewer tiles than bins, where a
 // piece is at most below_one_round elements; else from `rounds` whole rounds
-// on (negative: never), where a piece is at most three quarters of a tile.
+// on, where a piece is at most three quarters of a tile.
 struct Cut {
     int rounds = 0;
     int64_t below_one_round = 768;

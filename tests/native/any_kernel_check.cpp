@@ -18,7 +18,7 @@ static void check(bool ok, const char* what, int64_t a = 0, int64_t b = 0) {
 // The load of `keys` dealt over `bins` of a device of `waves` waves.
 static TileLoad dealt(const std::vector<int64_t>& keys, int bins, int64_t waves) {
     Plan p;
-    if (!build_dealt(int(keys.size()), keys.data(), kTileElems, 100, bins, &p, Cut{-1, 0}).empty()) std::exit(2);
+    if (!build_dealt(int(keys.size()), keys.data(), kTileElems, 100, bins, &p, Cut{1 << 30, 0}).empty()) std::exit(2);
     TileLoad l{0, 0, 0, 0, waves};
     for (int b = 0; b < bins; ++b) {
         int64_t tiles = 0;

@@ -20,7 +20,7 @@ int main() {
     int cut_plans = 0;
     for (int bins : {1, 8, 1024})
         for (int64_t tiles : {1, 3, 4, 7, 8, 9, 400, 586, 1023, 1024, 1025, 1327, 1500, 2047, 2048, 4600, 9000})
-            for (const Cut cut : {Cut{-1, 0}, Cut{-1, 512}, Cut{0, 768}, Cut{1, 512}, Cut{8, 512}}) {
+            for (const Cut cut : {Cut{1 << 30, 0}, Cut{16, 512}, Cut{0, 768}, Cut{1, 512}, Cut{8, 512}}) {
                 const std::vector<int64_t> keys = {tiles / 2 * tile, (tiles - tiles / 2) * tile + 5};
                 phub::Plan p;
                 if (!phub::build_dealt(2, keys.data(), tile, 48, bins, &p, cut).empty()) return 2;
@@ -32,7 +32,7 @@ int main() {
                     }
                 const bool below = tiles < bins;
                 const bool may = below ? cut.below_one_round > 0
-                                       : cut.rounds >= 0 && tiles / bins >= cut.rounds && tiles % bins != 0;
+                                       : tiles / bins >= cut.rounds && tiles % bins != 0;
                 check(may || pieces == 0, "cut", tiles, bins);
                 check(longest <= (below ? cut.below_one_round : 768), "piece", tiles, bins);
                 check(pieces > 0 || int64_t(p.segments.size()) == tiles + 1, "segments", tiles, bins);
@@ -52,11 +52,11 @@ int main() {
             const bool fixed = phub::has_fixed_kernel(n), burst = fixed && phub::burst_write_back(n, s);
             const bool adam_stream = fixed && s == 3 && n >= 7 && !burst;
             const Cut c = phub::cut_rule(n, s, true, false);
-            check(c.rounds == (!fixed ? 8 : burst ? 0 : adam_stream ? 2 : -1), "rule: streamed", n, s);
+            check(c.rounds == (!fixed ? 8 : burst ? 0 : adam_stream ? 2 : 16), "rule: streamed", n, s);
             check(c.below_one_round == (burst ? 768 : 512), "rule: short", n, s);
-            check(phub::cut_rule(n, s, false, false).rounds < 0, "rule: cached", n, s);
+            check(phub::cut_rule(n, s, false, false).rounds == (burst ? 4 : 16), "rule: cached", n, s);
             check(phub::cut_rule(n, s, false, false).below_one_round == c.below_one_round, "rule: cached", n, s);
-            check(phub::cut_rule(n, s, true, true).rounds < 0, "rule: unfused", n, s);
+            check(phub::cut_rule(n, s, true, true).rounds == 16, "rule: unfused", n, s);
         }
     std::printf("%d cut\n", cut_plans);
     return 0;

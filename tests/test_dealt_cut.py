@@ -23,17 +23,17 @@ def test_rule_and_plans(tmp_path):
 
 
 # below one whole round on 8 waves, by the tiles left over: a piece is 3/7 and
-# 4/7 of a tile (to 64 elements); then two and eight whole rounds and four tiles
-LEFT = (3, 4, 20, 68)
-BURST, PIECEWISE, CACHED = (3, 4, 20, 68), (3,), (3, 4)
+# 4/7 of a tile (to 64 elements); then 2, 4, 8 and 16 whole rounds and four tiles
+LEFT = (3, 4, 20, 36, 68, 132)
+BURST, CACHED, PIECEWISE, ANY = (3, 4, 20, 36, 68, 132), (3, 4, 36, 68, 132), (3, 132), (3, 68, 132)
 
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("n,opt,kw,cut", [
     (8, None, {}, BURST), (6, "sgd", {}, BURST), (14, "adam", {}, BURST), (32, None, {}, BURST),
     (1, "adam", {}, PIECEWISE), (4, None, {}, PIECEWISE), (8, "adam", {}, PIECEWISE),
-    (8, "adam", {"resident_bytes": 0}, (3, 20, 68)),
-    (17, None, {"resident_bytes": 0}, (3, 68)), (21, "adam", {"resident_bytes": 0}, (3, 68)),
+    (8, "adam", {"resident_bytes": 0}, (3, 20, 36, 68, 132)),
+    (17, None, {"resident_bytes": 0}, ANY), (21, "adam", {"resident_bytes": 0}, ANY),
     (8, None, {"resident_bytes": 1 << 28}, CACHED), (8, None, {"unfused": True}, PIECEWISE)])
 def test_segments_of_jobs(n, opt, kw, cut):
     from paper_1805_07891_amd.job import TorchJob
