@@ -34,14 +34,33 @@
 
 namespace phub {
 
+namespace {
+
+template <int OPT>
+__global__ __launch_bounds__(kBlockThreads)
+    __attribute__((amdgpu_waves_per_eu(1, 1))) void fused_step_many(PHUB_KERNEL_ARGS) {
+    constexpr int T = stash_tiles(kStates<OPT>);
+    __shared__ f4 stash_lds[kManyStash<T, OPT>];
+    walk_many<T, OPT>(PHUB_MANY_ARGS, (PHUB_LDS f4*)stash_lds);
+}
+
+template <int OPT>
+hipError_t launch(const StepParams& p, int grid, hipStream_t stream) {
+    hipLaunchKernelGGL((fused_step_many<OPT>), dim3(grid), dim3(kBlockThreads), 0, stream,
+                       PHUB_MANY_LAUNCH_ARGS);
+    return hipGetLastError();
+}
+
+}  // namespace
+
 hipError_t launch_fused_step_many(const StepParams& p, int optimizer, int grid,
                                   hipStream_t stream) {
     if (!many_takes(p)) return hipErrorInvalidValue;
     switch (optimizer) {
-        case kOptMomentum: return launch_many<stash_tiles(2), kOptMomentum>(p, grid, stream);
-        case kOptNesterov: return launch_many<stash_tiles(2), kOptNesterov>(p, grid, stream);
-        case kOptSgd: return launch_many<stash_tiles(1), kOptSgd>(p, grid, stream);
-        case kOptAdam: return launch_many<stash_tiles(3), kOptAdam>(p, grid, stream);
+        case kOptMomentum: return launch<kOptMomentum>(p, grid, stream);
+        case kOptNesterov: return launch<kOptNesterov>(p, grid, stream);
+        case kOptSgd: return launch<kOptSgd>(p, grid, stream);
+        case kOptAdam: return launch<kOptAdam>(p, grid, stream);
         default: return hipErrorInvalidValue;
     }
 }

@@ -1,5 +1,5 @@
-// The any-N stream kernel (fused_many.hip says what it does and why), for a
-// stash of T tiles a wave.
+// The walk of the any-N stream kernels (fused_many.hip says what it does and
+// why), for a stash of T tiles a wave.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -61,18 +61,20 @@ __device__ __forceinline__ void walk_ragged(const DevRem* __restrict__ rems, int
     }
 }
 
+// float4 of a workgroup's stash of T tiles a wave
 template <int T, int OPT>
-__global__ __launch_bounds__(kBlockThreads)
-    __attribute__((amdgpu_waves_per_eu(1, 1))) void fused_step_many(PHUB_KERNEL_ARGS) {
+constexpr int kManyStash = kWavesPerBlock * T * kVecPerLane * kStates<OPT> * 64;
+
+// A wave's whole work; stash_lds: the workgroup's stash.
+template <int T, int OPT>
+__device__ __forceinline__ void walk_many(PHUB_KERNEL_ARGS, PHUB_LDS f4* stash_lds) {
     constexpr int B = kManyBlock;
     static_assert(kMaxFixedWorkers >= B, "every piece takes at least two blocks");
     float* const state[3] = {weights, moments, second};
     const uint32_t wave = wave_index();
-    constexpr int S = kStates<OPT>;
     constexpr int P = T * kVecPerLane;  // pieces of the stash
-    __shared__ f4 stash_lds[kWavesPerBlock * P * S * 64];
-    PHUB_LDS f4* stash = (PHUB_LDS f4*)stash_lds + (threadIdx.x >> 6) * (P * S * 64) +
-                         (threadIdx.x & 63u);
+    PHUB_LDS f4* stash =
+        stash_lds + (threadIdx.x >> 6) * (P * kStates<OPT> * 64) + (threadIdx.x & 63u);
     const WaveHead h = heads[wave];
     walk_units<B, OPT, false, P>(tiles, h.tiles_streamed[0], h.tiles_streamed[1], grads,
                                  num_workers, state, o, stash);
@@ -85,17 +87,15 @@ __global__ __launch_bounds__(kBlockThreads)
     walk_ragged<OPT>(rems, h.rems_streamed[0], h.rems_streamed[1], grads, num_workers, state, o);
     walk_ragged<OPT>(rems, h.rems_resident[0], h.rems_resident[1], grads, num_workers, state, o);
 }
+#define PHUB_MANY_ARGS                                                                       \
+    tiles, tile_begin, rems, rem_begin, heads, grads, outs, weights, moments, second, o,     \
+        num_workers, pool, pool_count, pool_counters, pool_launch
+#define PHUB_MANY_LAUNCH_ARGS                                                                \
+    p.tiles, p.tile_begin, p.rems, p.rem_begin, p.heads, p.grads, p.outs, p.weights,         \
+        p.moments, p.second, p.opt, p.num_workers, p.pool, p.pool_count, p.pool_counters,    \
+        p.pool_launch
 
-template <int T, int OPT>
-hipError_t launch_many(const StepParams& p, int grid, hipStream_t stream) {
-    hipLaunchKernelGGL((fused_step_many<T, OPT>), dim3(grid), dim3(kBlockThreads), 0, stream,
-                       p.tiles, p.tile_begin, p.rems, p.rem_begin, p.heads, p.grads, p.outs,
-                       p.weights, p.moments, p.second, p.opt, p.num_workers, p.pool, p.pool_count,
-                       p.pool_counters, p.pool_launch);
-    return hipGetLastError();
-}
-
-// Whether the any-N stream kernel can take a step.
+// Whether the any-N stream kernels can take a step.
 inline bool many_takes(const StepParams& p) {
     // (a piece takes at least two blocks: the window's pointers run one ahead)
     return p.num_workers > kManyBlock && !p.outs && !p.merge && p.pool_count == 0;

@@ -26,15 +26,18 @@ def test_the_shared_stash_leaves_room_for_a_second_launch(tmp_path):
     blocks = asm.split("  - .agpr_count:")[1:]
     assert len(blocks) == 4
     for block in blocks:
-        tiles, opt = map(int, re.search(r"fused_step_manyILi(\d+)ELi(\d)E", block).groups())
+        name = re.search(r"\.name:\s+(\S+)", block).group(1)
+        opt = int(re.search(r"fused_step_many_sharedILi(\d)E", name).group(1))
 
         def field(key):
             return int(re.search(rf"\.{key}:\s+(\d+)", block).group(1))
 
         states = {0: 2, 1: 2, 2: 1, 3: 3}[opt]
-        assert tiles == 4 // states
-        assert field("group_segment_fixed_size") == 4 * tiles * states * 4096 <= 80 * 1024
-        assert field("vgpr_count") <= 128  # more than one wave per SIMD
+        lds = field("group_segment_fixed_size")
+        assert lds == 4 * (4 // states) * states * 4096 <= 80 * 1024
+        # the registers that the launch claims leave room for as many waves
+        claimed = re.search(rf"\.amdhsa_kernel {name}\n(?:.*\n)*?.*\.amdhsa_next_free_vgpr (\d+)", asm)
+        assert 512 // (-(-int(claimed.group(1)) // 8) * 8) >= 160 * 1024 // lds
         assert field("private_segment_fixed_size") == 0 and field("vgpr_spill_count") == 0
 
 
