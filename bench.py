@@ -39,6 +39,8 @@ HBM_PEAK_GBS = 8000.0
 KERNEL_SOURCES = ["paper_1805_07891_amd/csrc/fused_step.hip",
                   "paper_1805_07891_amd/csrc/fused_stream.hip",
                   "paper_1805_07891_amd/csrc/fused_many.hip",
+                  "paper_1805_07891_amd/csrc/fused_many_shared.hip",
+                  "paper_1805_07891_amd/csrc/many_walk.hpp",
                   "paper_1805_07891_amd/csrc/tile_walk.hpp",
                   "paper_1805_07891_amd/csrc/stream_walk.hpp",
                   "paper_1805_07891_amd/csrc/device.hpp", "paper_1805_07891_amd/csrc/kernels.hpp",

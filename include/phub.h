@@ -191,10 +191,11 @@ typedef struct phub_options {
                                1 keeps every chunk of chunk_bytes an
                                indivisible item of the LPT schedule, as in
                                the paper (no splitting of chunks however few
-                               they are).  0 (default): while there are fewer
-                               than 128 items per wave, chunks are halved, not
-                               below 1024 elements, so that every wave has
-                               work.  Results do not depend on it. */
+                               they are).  0 (default): chunks are divisible;
+                               the LPT schedule deals the keys in pieces of at
+                               most 1024 elements whatever chunk_bytes is,
+                               from 4096 bytes on (smaller chunks stay items
+                               of their own).  Results do not depend on it. */
 } phub_options;
 
 /*
@@ -397,15 +398,15 @@ int phub_destroy(phub_job *job);
  *   hip_stream    the hipStream_t the step is ordered on (NULL = the null
  *                 stream).
  * The step's schedule and pointer table live in a device array of the
- * library of 4 MiB (PHUB_NOALLOC_SCRATCH_BYTES), one per GPU, held until
- * the process ends; that bounds a call to about 240 M parameters and
- * PHUB_EINVAL reports a step that does not fit, before anything is
- * enqueued.  The call sends its tables on hip_stream after the stream's
+ * library of 4 MiB (PHUB_NOALLOC_SCRATCH_BYTES), and one entry per key in
+ * another of 2.7 MiB; each GPU has both, held until the process ends.  The
+ * first bounds a call to about 240 M parameters and PHUB_EINVAL reports a
+ * step that does not fit, before anything is enqueued.  The call sends its tables on hip_stream after the stream's
  * earlier work and builds the schedule on the GPU; the step's kernel runs
  * asynchronously.  (Only a call with more than about 7600 gradient pointers
  * and keys waits for its upload, and so for the stream's earlier work.)
  * A stream that is being captured is refused (PHUB_EHIP).
- * Calls on one GPU share its array: calls that overlap on one GPU (from
+ * Calls on one GPU share its arrays: calls that overlap on one GPU (from
  * other threads, or on another stream before this call's kernel has run)
  * race and give wrong results.  All state streams non-temporally (nothing
  * is kept in the memory-side cache).  Errors: PHUB_EINVAL, PHUB_ENOMEM (host
@@ -421,9 +422,10 @@ int phub_step_noalloc(int num_workers, int num_keys, const int64_t *key_elems,
 const char *phub_last_error(void);
 
 /* --------------------------------------------------------------------------
- * The chunk schedule (section 3.2.4), computed on the host only.  phub_init
- * runs it; it is exported so that its coverage and balance can be checked
- * without a GPU.
+ * The chunk schedule (section 3.2.4), computed on the host only and exported
+ * so that its coverage and balance can be checked without a GPU.  phub_init
+ * runs it for PHUB_SCHEDULE_SPLIT, for whole_chunks and for chunks below 4096
+ * bytes; the default is the same partition at another granularity (below).
  *
  * The unit that plays a PHub core is one wave (64 lanes) of the fused
  * kernel; the kernel runs one persistent workgroup per compute unit, and
@@ -451,7 +453,10 @@ const char *phub_last_error(void);
  * of 4 waves per compute unit).  For LPT it deals the same partition at the
  * kernels' granularity (full 1024-element tiles in turn, then what is left
  * over and the keys' ends, largest first to the least loaded wave, small
- * keys not bundled), except with whole_chunks or chunks below 4096 bytes.
+ * keys not bundled), except with whole_chunks or chunks below 4096 bytes;
+ * PHUB_SCHEDULE_DYNAMIC with a tile pool takes LPT's items (min_items 128 per
+ * bin) for what is not in the pool.  phub_plan_build does not show a dealt
+ * schedule; phub_job_info counts its segments.
  * ------------------------------------------------------------------------ */
 
 /* One contiguous run of one key handled by one wave. */

@@ -19,7 +19,7 @@
 // same loads without the state stores ran at 0.88-0.97 of peak, with a
 // piece's stores issued as soon as it is done at 0.71-0.73, though they are
 // 3-10% of the bytes.  So the tiles' state is written back in bursts in the
-// chip-wide write phases, as in fused_step.hip.  Measured (MI355X, 25.6 M
+// chip-wide write phases, as in tile_walk.hpp.  Measured (MI355X, 25.6 M
 // parameters, momentum, nothing cached, fraction of 8 TB/s; before: batches
 // of eight workers' loads issued together and drained, stores piece by
 // piece): 17 workers 0.710 -> 0.821, 21 0.719 -> 0.841, 33 0.707 -> 0.855,

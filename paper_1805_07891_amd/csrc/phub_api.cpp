@@ -823,11 +823,11 @@ int phub_init_ex(phub_job** out, int num_workers, int num_keys, const int64_t* k
                         // otherwise or makes them smaller than a tile.
                         // Dealt tile by tile against the chunk items'
                         // bundles (MI355X): 0.25 M parameters in 442 keys,
-                        // 1 worker, Adam 17.1 -> 5.9 us; 0.3 M in 300, 16,
-                        // Adam 26.0 -> 14.2; 0.63 M in 271, 21, Adam 33.9
-                        // -> 19.4; 6.4 M in 40, 8 workers 52.6 -> 50.8;
+                        // 1 worker, Adam 12.4 -> 6.1 us; 0.3 M in 300, 16,
+                        // Adam 17.2 -> 14.2; 0.63 M in 271, 21, Adam 43.1
+                        // -> 16.1; 6.4 M in 40, 8 workers 51.2 -> 49.0;
                         // 25.6 M in 161, 8 workers 189.4 -> 187.3, 16
-                        // workers 309.9 -> 305.6; others level.
+                        // workers 309.9 -> 305.6.
                         if (!split && !j->dynamic && !whole_chunks &&
                             chunk_bytes >= phub::kTileElems * int64_t(sizeof(float)))
                             err = phub::build_dealt(int(vk.size()), elems.data(), phub::kTileElems,

@@ -4,8 +4,9 @@
 // not call hipMalloc, harnesses that forbid allocation).  The caller passes
 // the gradients and the master weights and momentum; everything else the
 // fused kernel reads (the chunk schedule of section 3.2.4 in its device form
-// and the gradient pointer table) goes into `scratch` below, a file-scope
-// device array that each GPU holds for the life of the process.  The kernel
+// and the gradient pointer table) goes into `scratch` below, and the key
+// entries it is built from into `key_entries`: file-scope device arrays that
+// each GPU holds for the life of the process (4 and 2.7 MiB).  The kernel
 // is the job path's fused kernel, so the results are those of phub_init +
 // phub_push_all + phub_step on the same inputs (they do not depend on the
 // schedule).
@@ -21,10 +22,9 @@
 // workers, a call): schedule built on the host, copied and waited for 1976
 // us, this 201 us, of which the step's kernel takes 190.
 //
-// The array's name in host code is a host-side stand-in, not a device
-// address: its device address is taken once per device with
-// hipGetSymbolAddress, with that device current, and only that address is
-// used from host code.
+// An array's name in host code is a host-side stand-in, not a device address:
+// its device address is taken once per device with hipGetSymbolAddress, with
+// that device current, and only that address is used from host code.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

@@ -89,11 +89,12 @@ __device__ __forceinline__ const float* lane_base(uint64_t p, int j) {
     return reinterpret_cast<const float*>((uint64_t(hi) << 32) | lo);
 }
 
-// Burst write-back of the streamed tiles' state, as in fused_step.hip: a
-// finished piece's state goes to a stash in LDS (P pieces per wave, lane l holding entry l of every 64), and the wave writes the stash
-// back in one run of stores when the chip-wide write window is open (looked
-// at after every block of loads), when the stash is full, or after its last
-// piece.  Each lane reads back only what it wrote: no barrier.
+// Burst write-back of the streamed tiles' state, as in tile_walk.hpp: a
+// finished piece's state goes to a stash in LDS (P pieces per wave, lane l
+// holding entry l of every 64), and the wave writes the stash back in one run
+// of stores when the chip-wide write window is open (looked at after every
+// block of loads), when the stash is full, or after its last piece.  Each
+// lane reads back only what it wrote: no barrier.
 template <int S>
 struct Stash {
     PHUB_LDS f4* lds;  // the lane's entry of the wave's first piece
