@@ -93,11 +93,10 @@ constexpr bool has_fixed_kernel(int num_workers) {
 // writes the streamed bin's state back in bursts through LDS, in the
 // chip-wide write phases below (the stream walk always does: with Adam from
 // 7 workers, kStreamBlock): from 6 workers for momentum and plain SGD, from
-// 14 for Adam (measured on
-// MI355X with nothing cached, against piece-by-piece write-back: momentum
-// with 6-16 workers +0.7 to +4.5 points, plain SGD with 6-16 up to +0.8,
-// Adam with 14 and 16 +2.7 and +1.7; with fewer workers 1.5 to 15 points
-// slower).  num_states: 1 plain SGD, 2 momentum, 3 Adam.
+// 14 for Adam (measured on MI355X with nothing cached, against piece-by-piece
+// write-back: momentum with 6-16 workers +0.7 to +4.5 points, plain SGD with
+// 6-16 up to +0.8, Adam with 14 and 16 +2.7 and +1.7; with fewer workers 1.5
+// to 15 points slower).  num_states: 1 plain SGD, 2 momentum, 3 Adam.
 constexpr int kBurstMinWorkers[3] = {6, 6, 14};
 
 constexpr bool burst_write_back(int num_workers, int num_states) {
